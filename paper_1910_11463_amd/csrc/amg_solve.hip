@@ -664,28 +664,112 @@ k_hex_norm_partial(int chunks, const int64_t* __restrict__ moff, const int64_t* 
     if (threadIdx.x == 0) partial[static_cast<int64_t>(m) * chunks + chunk] = acc;
 }
 
+// Swap with the lane whose number differs in bit 0 (BIT = 0) or bit 1 (BIT = 1).
+template <int BIT>
+__device__ __forceinline__ double quad_swap(double v) {
+    constexpr int kPerm = BIT == 0 ? 0xB1 : 0x4E;      // quad_perm [1,0,3,2] / [2,3,0,1]
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_update_dpp(0, lo, kPerm, 0xf, 0xf, true);
+    hi = __builtin_amdgcn_update_dpp(0, hi, kPerm, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// A member's array as a tile sweep sees it: places are bytes from its start; a
+// place of kNone (moved by any offset the sweep adds) or kOut and more reads
+// zero and is not written.  Members of at most 1 GiB of x use buffer
+// instructions, whose range check does the masking: every load and store of a
+// step is issued without a branch and the compiler's wait counts stay exact.
+template <bool BIG>
+struct TileVec;
+
+template <>
+struct TileVec<false> {
+    using Place = uint32_t;
+    static constexpr uint32_t kNone = 0x80000000u, kOut = 0x40000000u;
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ TileVec(const void* p, uint64_t bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes), 0x00027000)) {}
+    __device__ __forceinline__ double load(Place at) const {
+        typedef unsigned v2u __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(double, static_cast<v2u>(__builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0)));
+    }
+    __device__ __forceinline__ double2 load2(Place at) const {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        return __builtin_bit_cast(double2, static_cast<v4u>(__builtin_amdgcn_raw_buffer_load_b128(r, at, 0, 0)));
+    }
+    __device__ __forceinline__ void store2(Place at, double2 v) const {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, at, 0, 0);
+    }
+};
+
+template <>
+struct TileVec<true> {
+    using Place = uint64_t;
+    static constexpr uint64_t kNone = uint64_t(1) << 62, kOut = uint64_t(1) << 61;
+    char* p;
+    uint64_t bytes;
+    __device__ __forceinline__ TileVec(const void* q, uint64_t n)
+        : p(const_cast<char*>(static_cast<const char*>(q))), bytes(n) {}
+    __device__ __forceinline__ double load(Place at) const {
+        return at < bytes ? *reinterpret_cast<const double*>(p + at) : 0.0;
+    }
+    __device__ __forceinline__ double2 load2(Place at) const {
+        return at < bytes ? *reinterpret_cast<const double2*>(p + at) : make_double2(0.0, 0.0);
+    }
+    __device__ __forceinline__ void store2(Place at, double2 v) const {
+        if (at < bytes) *reinterpret_cast<double2*>(p + at) = v;
+    }
+};
+
 // Tile sweep: block Jacobi over boxes of TXY x TXY x tz elements with an exact
 // solve inside each box (the relaxation by an on-processor solve of Sec. "Use
 // of Algebraic Multigrid", a box standing for a processor).  Within a box the
 // upwind operator is block lower triangular with identity diagonal blocks, so
 // the box solve is a forward substitution x_e = b_e - D_e^{-1} A_eU x_U in
 // upwind order.  A block per box runs it as a wavefront: primed coordinates
-// count from the box's inflow corner; thread (i', j') owns a column of the box
-// and at step s solves element k' = s - i' - j', whose x- and y-upwind
-// neighbours were solved at step s - 1 by threads (i'-1, j') and (i', j'-1)
-// (read from LDS) and whose z-upwind neighbour is its own previous element
-// (kept in registers).  Neighbours outside the box enter with their values in
-// xin (the previous iterate; none when xin_zero).  Boxes at the mesh's far
-// side are cut by it; a grid of members x boxes.
-template <int TXY>
-__global__ void __launch_bounds__(TXY * TXY)
+// count from the box's inflow corner; column (i', j') of the box solves its
+// element k' = s - i' - j' at step s, whose x- and y-upwind neighbours were
+// solved at step s - 1 by columns (i'-1, j') and (i', j'-1) (read from LDS) and
+// whose z-upwind neighbour is the column's own previous element (kept in
+// registers).  Neighbours outside the box enter with their values in xin (the
+// previous iterate; none when xin_zero).  Boxes at the mesh's far side are cut
+// by it; a grid of members x boxes.
+//
+// What bounds it: the steps are a serial chain, w_x + w_y + w_z - 2 of them
+// with a barrier each.  Four lanes (a quad) take an element: the lane of nodes
+// (a_x', a_y') (counted from the inflow side, like every node here) holds a_z' = 0
+// and 1, the transforms of the Kronecker-sum solve (hex_face_solve_den) along y
+// and x are one exchange inside the quad each (DPP), and each lane divides by
+// one of the four eigenvalue sums.  Against one lane per element that is a
+// third of the instructions per step and wave, and with 16 x 16 boxes four waves
+// per SIMD instead of one.  b, sigma_t and the outside neighbours' faces are
+// loaded kAhead steps before they are used (a lane's share is small enough to
+// keep in registers for so long); the faces go to the rim of the exchange
+// buffer one step before, so that every column reads its neighbours alike.
+// A step takes 1.1-1.2 us with little else on the chip (2 us with one lane per
+// element), about 115 vector instructions and 8 memory instructions per wave.
+// us per launch, one stream, one lane per element -> here: 64^3, 8 directions
+// 194 -> 145; 64^3, 1 direction (16 blocks) 168 -> 108; 48^3, 16 directions
+// 157 -> 118; 32^3, 80 directions (320 blocks on 256 CUs) 221 -> 192.  More
+// memory instructions with fewer vector ones (8-byte loads and stores, no
+// exchange of shares: 105 and 11) took 179 / 137 / 143 / 236 us.
+constexpr int kAhead = 4;
+
+template <int TXY, bool BIG>
+__global__ void __launch_bounds__(4 * TXY * TXY)
 k_hex_tile(uint32_t E, int nx, int ny, int nz, int tz, int mx, int my, int mz,
            const double* __restrict__ kap, const int32_t* __restrict__ inflow,
            const double* __restrict__ sigt, const uint8_t* __restrict__ active,
            const uint8_t* __restrict__ relax, const double* __restrict__ b,
            const double* __restrict__ xin, double* __restrict__ xout, int xin_zero) {
-    constexpr int NT = TXY * TXY;
-    __shared__ double sh[2][8][NT];
+    using Vec = TileVec<BIG>;
+    using Place = typename Vec::Place;
+    using SPlace = std::make_signed_t<Place>;
+    constexpr int W = TXY + 1;                          // quads per row of the exchange buffer
+    constexpr double kS2 = kHexS2;
+    constexpr double kC = 0.70710678118654752440;       // 1 / sqrt 2
+    __shared__ double2 sh[2][4 * W * W];                // nodes a_z' = 0, 1; row and column 0: outside the box
     const uint32_t per = static_cast<uint32_t>(mx) * static_cast<uint32_t>(my) * static_cast<uint32_t>(mz);
     const uint32_t m = blockIdx.x / per;
     uint32_t t = blockIdx.x - m * per;
@@ -699,7 +783,8 @@ k_hex_tile(uint32_t E, int nx, int ny, int nz, int tz, int mx, int my, int mz,
     const int x0 = ti * TXY, y0 = tj * TXY, z0 = tk * tz;
     const int wx = min(TXY, nx - x0), wy = min(TXY, ny - y0), wz = min(tz, nz - z0);
     const int tid = static_cast<int>(threadIdx.x);
-    const int ip = tid % TXY, jp = tid / TXY;
+    const int px = tid & 1, py = (tid >> 1) & 1;        // a_x', a_y'
+    const int ip = (tid >> 2) % TXY, jp = (tid >> 2) / TXY;
     const bool lane = ip < wx && jp < wy;
     const int i = x0 + (sx ? wx - 1 - ip : ip);
     const int j = y0 + (sy ? wy - 1 - jp : jp);
@@ -708,115 +793,143 @@ k_hex_tile(uint32_t E, int nx, int ny, int nz, int tz, int mx, int my, int mz,
     const bool outy = jp == 0 && !xin_zero && (sy ? j + 1 < ny : j > 0);
     const bool outz = !xin_zero && (sz ? z0 + wz < nz : z0 > 0);
     const int64_t nxy = static_cast<int64_t>(nx) * ny;
-    const int64_t mbase = static_cast<int64_t>(m) * E;
-    const int64_t col = mbase + static_cast<int64_t>(j) * nx + i;
+    const uint64_t bytes = static_cast<uint64_t>(E) * 64;
+    const int64_t mrow = static_cast<int64_t>(m) * E * 8;
+    const Vec vb(b + mrow, bytes), vin(xin + mrow, bytes), vout(xout + mrow, bytes);
+    const Vec vsig(sigt, static_cast<uint64_t>(E) * 8);
+    // byte of node (a_x', a_y', a_z') in an element; the 16-byte share that this
+    // lane loads and stores: both a_x at (a_y', a_z' = its a_x')
+    auto node = [&](int ax, int ay, int az) { return 8 * ((ax ^ sx) + 2 * (ay ^ sy) + 4 * (az ^ sz)); };
+    const int here = 16 * (py ^ sy) + 32 * (px ^ sz);
+    // a share into the lane's nodes a_z' = 0, 1, and back: one exchange with the
+    // lane of the other a_x'
+    const bool hi = (px ^ sx) != 0;
+    auto take = [&](double2 v) {
+        const double keep = hi ? v.y : v.x, o = quad_swap<0>(hi ? v.x : v.y);
+        return px ? make_double2(o, keep) : make_double2(keep, o);
+    };
+    auto give = [&](double2 v) {
+        const double keep = px ? v.y : v.x, o = quad_swap<0>(px ? v.x : v.y);
+        return hi ? make_double2(o, keep) : make_double2(keep, o);
+    };
     const int kfirst = sz ? z0 + wz - 1 : z0;
-    const int dk = sz ? -1 : 1;
+    const SPlace dk = static_cast<SPlace>((sz ? -nxy : nxy) * 64);
+    const int lag = ip + jp;
+    const unsigned depth = lane ? static_cast<unsigned>(wz) : 0u;
+    // the lane's place in the column's element of the next step to load, and its k'
+    Place at = static_cast<Place>((static_cast<int64_t>(kfirst) * nxy + static_cast<int64_t>(j) * nx + i) * 64 + here);
+    const Place at_z = at - static_cast<Place>(dk) + static_cast<Place>(static_cast<SPlace>(node(px, py, 1) - here));   // z-upwind outflow face
+    at -= static_cast<Place>(static_cast<SPlace>(lag) * dk);
+    int kp = -lag;
     // stores by whole 128-byte pairs: elements i and i ^ 1 of one x-row share a
-    // line (when nx is even); the later of the two lanes (larger ip: one step
+    // line (when nx is even); the later of the two columns (larger ip: one step
     // later, same z) writes both, the partner's values from the exchange
     // buffer, the earlier stores nothing; an element without a partner in
     // the box stores alone
     const int ipart = i ^ 1;
     const bool pin = lane && ipart >= x0 && ipart < x0 + wx;
     const int ip_part = sx ? x0 + wx - 1 - ipart : ipart - x0;
-    const bool store_pair = pin && ip_part == ip - 1;
-    const bool store_none = pin && ip_part == ip + 1;
-    double zf[4] = {0.0, 0.0, 0.0, 0.0};    // z-upwind face of the column's last element
-    const int nsteps = wx + wy + wz - 2;
-    // the column's elements in order: sigma_t loaded two elements ahead and the
-    // eigenvalue reciprocals formed one element ahead, off the step's chain
-    const int64_t cbase = col - mbase + static_cast<int64_t>(kfirst) * nxy;
-    const int64_t cstep = static_cast<int64_t>(dk) * nxy;
-    HexDen den = hex_den(lane && wz > 0 ? sigt[cbase] : 0.0, dr);
-    double sig_n = lane && wz > 1 ? sigt[cbase + cstep] : 0.0;
-    // b of the column's next element and, for the lanes on the box's inflow
-    // sides, the face values of its x- and y-upwind neighbours outside the box:
-    // loaded at the end of a step (after its stores), first used after the next
-    // step's barrier
-    double bv[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double ox[4] = {0.0, 0.0, 0.0, 0.0}, oy[4] = {0.0, 0.0, 0.0, 0.0};
-    auto load_next = [&](int64_t gn) {
-        load8(b + gn * 8, bv);
-        if (outx) {
-            const double* xu = xin + (gn + (sx ? 1 : -1)) * 8 + (1 - sx);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) ox[q] = xu[2 * q];
-        }
-        if (outy) {
-            const double2* xu = reinterpret_cast<const double2*>(
-                xin + (gn + (sy ? nx : -static_cast<int64_t>(nx))) * 8 + 2 * (1 - sy));
-            const double2 lo = xu[0], hi = xu[2];
-            oy[0] = lo.x; oy[1] = lo.y; oy[2] = hi.x; oy[3] = hi.y;
-        }
+    const Place own = !(pin && ip_part == ip + 1) ? 0 : Vec::kOut;
+    const Place partner = pin && ip_part == ip - 1 ? static_cast<Place>((i & 1) ? SPlace(-64) : SPlace(64)) : Vec::kOut;
+    // outside neighbours' outflow faces: this lane fetches one of the two a_z'
+    const Place to_x = outx ? static_cast<Place>(static_cast<SPlace>((sx ? 64 : -64) + node(1, py, px) - here)) : Vec::kOut;
+    const Place to_y = outy ? static_cast<Place>(static_cast<SPlace>((sy ? nx : -static_cast<int64_t>(nx)) * 64 +
+                                                                     node(px, 1, py) - here)) : Vec::kOut;
+    // the exchange buffer: this lane, the x- and y-upwind elements' outflow faces,
+    // the x-upwind element's share, the rim entries this lane fills
+    const int me = 4 * ((jp + 1) * W + ip + 1) + (tid & 3);
+    const int from_x = 4 * ((jp + 1) * W + ip) + 1 + 2 * py;
+    const int from_y = 4 * (jp * W + ip + 1) + px + 2;
+    const int from_p = 4 * ((jp + 1) * W + ip) + 2 * py;
+    const int rim_x = 2 * (4 * ((jp + 1) * W) + 1 + 2 * py) + px;
+    const int rim_y = 2 * (4 * (ip + 1) + px + 2) + py;
+    // the transforms W^{-1} scaled by 2 per axis and the doubled real part
+    // folded into the face coefficients: 2 / 8
+    const double al0 = dr.kap[0] * (px == 0 ? -1.0 : 0.5);
+    const double al1 = dr.kap[1] * (py == 0 ? -1.0 : 0.5);
+    const double al2 = dr.kap[2];                                    // a_z' = 0: -al2, 1: al2 / 2
+    const double cx = px ? -kC : kC, cy = py ? -kC : kC;             // W^{-1}, eigen-index px / py
+    const double ex = px ? -1.0 : 1.0, ey = py ? -1.0 : 1.0;         // W: inflow-side node or the other
+    const double fx = px ? kS2 : 0.0, fy = py ? kS2 : 0.0;
+    const double kap2 = 2.0 * (dr.kap[0] + dr.kap[1] + dr.kap[2]);
+    const double mi = kHexS2 * ((px ? -dr.kap[0] : dr.kap[0]) + (py ? -dr.kap[1] : dr.kap[1]) + dr.kap[2]);
+
+    Place ro[kAhead];
+    double2 rb[kAhead];
+    double rox[kAhead], roy[kAhead], rsig[kAhead];
+    auto fetch = [&](int q) {
+        const Place o = static_cast<unsigned>(kp) < depth ? at : Vec::kNone;
+        at += static_cast<Place>(dk);
+        ++kp;
+        ro[q] = o;
+        rb[q] = vb.load2(o);
+        rox[q] = vin.load(o + to_x);
+        roy[q] = vin.load(o + to_y);
+        rsig[q] = vsig.load((o >> 6) << 3);
     };
-    if (lane && wz > 0) load_next(col + static_cast<int64_t>(kfirst) * nxy);
-    for (int s = 0; s < nsteps; ++s) {
-        const int kp = s - ip - jp;
-        const int p = s & 1;
-        if (lane && kp >= 0 && kp < wz) {
-            const int k = kfirst + dk * kp;
-            const int64_t g = col + static_cast<int64_t>(k) * nxy;
-            double v0[4], v1[4], v2[4];
-            if (ip > 0) {
+    auto fill_rim = [&](int p, int q) {
+        double* rim = reinterpret_cast<double*>(sh[p]);
+        if (ip == 0) rim[rim_x] = rox[q];
+        if (jp == 0) rim[rim_y] = roy[q];
+    };
+    // z-upwind face value of the column's next element
+    double zf = vin.load(lane && outz ? at_z : Vec::kNone);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v0[q] = sh[p ^ 1][(1 - sx) + 2 * q][tid - 1];
-            } else if (outx) {
+    for (int q = 0; q < kAhead; ++q) fetch(q);
+    // the first loads are waited for here: a load that may be pending from
+    // before the loop would be counted from there in every step
+    asm volatile("" : "+v"(zf));
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v0[q] = ox[q];
-            } else {
+    for (int q = 0; q < kAhead; ++q)
+        asm volatile("" : "+v"(rb[q].x), "+v"(rb[q].y), "+v"(rox[q]), "+v"(roy[q]), "+v"(rsig[q]));
+    fill_rim(1, 0);
+    double mr = kap2 + rsig[0], inv = 1.0 / (mr * mr + mi * mi);
+    const int nsteps = wx + wy + wz - 2;
+    __syncthreads();
+    for (int s0 = 0; s0 < nsteps; s0 += kAhead) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v0[q] = 0.0;
-            }
-            if (jp > 0) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v1[q] = sh[p ^ 1][2 * (1 - sy) + (q & 1) + 4 * (q >> 1)][tid - TXY];
-            } else if (outy) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v1[q] = oy[q];
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v1[q] = 0.0;
-            }
-            if (kp > 0) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v2[q] = zf[q];
-            } else if (outz) {
-                const double2* xu = reinterpret_cast<const double2*>(xin + (g + (sz ? nxy : -nxy)) * 8 + 4 * (1 - sz));
-                const double2 lo = xu[0], hi = xu[1];
-                v2[0] = lo.x; v2[1] = lo.y; v2[2] = hi.x; v2[3] = hi.y;
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v2[q] = 0.0;
-            }
-            double y[8], xn[8];
-            const HexDen den_n = hex_den(sig_n, dr);
-            hex_face_solve_den(den, dr, v0, v1, v2, y);
-            den = den_n;
-#pragma unroll
-            for (int a = 0; a < 8; ++a) xn[a] = bv[a] - y[a];
-            if (store_pair) {
-                double pv[8];
-#pragma unroll
-                for (int a = 0; a < 8; ++a) pv[a] = sh[p ^ 1][a][tid - 1];
-                if (i & 1) {
-                    store8(xout + (g - 1) * 8, pv);
-                    store8(xout + g * 8, xn);
-                } else {
-                    store8(xout + g * 8, xn);
-                    store8(xout + (g + 1) * 8, pv);
-                }
-            } else if (!store_none) {
-                store8(xout + g * 8, xn);
-            }
-#pragma unroll
-            for (int a = 0; a < 8; ++a) sh[p][a][tid] = xn[a];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) zf[q] = xn[4 * (1 - sz) + q];
-            if (kp + 1 < wz) load_next(g + cstep);
-            sig_n = kp + 2 < wz ? sigt[cbase + (kp + 2) * cstep] : 0.0;
+        for (int q = 0; q < kAhead; ++q) {
+            constexpr int kMask = kAhead - 1;
+            const int p = q & 1;       // kAhead is even
+            const double2 v0 = sh[p ^ 1][from_x], v1 = sh[p ^ 1][from_y];
+            const double* pp = reinterpret_cast<const double*>(&sh[p ^ 1][from_p]) + px;
+            const double2 ps = make_double2(pp[0], pp[2]);
+            // g = sum_d -kap_d M1^{-1}[a_d][s_d] v_d
+            const double g0 = al0 * v0.x + al1 * v1.x - al2 * zf;
+            const double g1 = al0 * v0.y + al1 * v1.y + 0.5 * al2 * zf;
+            // W^{-1} along z (eigen-index 0; the other is the conjugate)
+            const double ur = g0, ui = -kC * (g0 + g1);
+            // along y: this lane takes eigen-index py
+            const double uro = quad_swap<1>(ur), uio = quad_swap<1>(ui);
+            const double vr = (py ? uro : ur) + cy * (ui + uio);
+            const double vi = (py ? uio : ui) - cy * (ur + uro);
+            // along x: eigen-index px
+            const double vro = quad_swap<0>(vr), vio = quad_swap<0>(vi);
+            const double gr = (px ? vro : vr) + cx * (vi + vio);
+            const double gi = (px ? vio : vi) - cx * (vr + vro);
+            // divide by the eigenvalue sum mr + i mi
+            const double zr = (gr * mr + gi * mi) * inv, zi = (gi * mr - gr * mi) * inv;
+            // W along x, then y: this lane's node
+            const double zro = quad_swap<0>(zr), zio = quad_swap<0>(zi);
+            const double pr = ex * (zr + zro) + fx * (zi - zio);
+            const double pi = ex * (zi + zio) - fx * (zr - zro);
+            const double pro = quad_swap<1>(pr), pio = quad_swap<1>(pi);
+            const double qr = ey * (pr + pro) + fy * (pi - pio);
+            const double qi = ey * (pi + pio) - fy * (pr - pro);
+            // along z: inflow side q_r, the other side -(q_r + sqrt2 q_i)
+            const double2 bv = take(rb[q]);
+            const double2 xn = make_double2(bv.x - qr, bv.y + (qr + kS2 * qi));
+            sh[p][me] = xn;
+            const Place o = ro[q];
+            vout.store2(o + own, give(xn));
+            vout.store2(o + partner, sx ? make_double2(ps.y, ps.x) : ps);
+            zf = o < Vec::kOut ? xn.y : zf;
+            mr = kap2 + rsig[(q + 1) & kMask];
+            inv = 1.0 / (mr * mr + mi * mi);
+            fill_rim(p, (q + 1) & kMask);
+            fetch(q);
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -1456,14 +1569,15 @@ double* Hierarchy::sweeps(Level& L, int l, const std::string& sched, double* cur
             const int64_t blocks = members * mx * my * mz;
             PAIR_CHECK(blocks < (int64_t(1) << 31), "tile grid too large");
             int h = prof_begin(s_, kind);
-            if (txy == 8)
-                hipLaunchKernelGGL(k_hex_tile<8>, dim3(static_cast<unsigned>(blocks)), dim3(64), 0, s_,
+            // buffer instructions where a member's x and one y-row stay below 1 GiB
+            const bool big = (static_cast<int64_t>(E.E) + E.nx + 64) * 64 > (int64_t(1) << 30);
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(4 * txy * txy), 0, s_,
                                    static_cast<uint32_t>(E.E), E.nx, E.ny, E.nz, tz, mx, my, mz, E.kap.p,
                                    E.inflow.p, E.sigt.p, act, L.relax.p, L.b.p, cur, other, zero ? 1 : 0);
-            else
-                hipLaunchKernelGGL(k_hex_tile<16>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s_,
-                                   static_cast<uint32_t>(E.E), E.nx, E.ny, E.nz, tz, mx, my, mz, E.kap.p,
-                                   E.inflow.p, E.sigt.p, act, L.relax.p, L.b.p, cur, other, zero ? 1 : 0);
+            };
+            if (txy == 8) big ? launch(k_hex_tile<8, true>) : launch(k_hex_tile<8, false>);
+            else big ? launch(k_hex_tile<16, true>) : launch(k_hex_tile<16, false>);
             prof_end(s_, h, tile_relax_bytes(L, E, txy, tz, zero));
             PAIR_LAUNCH_CHECK();
             std::swap(cur, other);
