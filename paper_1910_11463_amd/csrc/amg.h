@@ -254,7 +254,8 @@ private:
     void build_level_aux(Level& L, int l);
     void coarse_setup(Level& L, const std::vector<int>& members);
     void vcycle_launches(bool x_is_zero);
-    double* sweeps(Level& L, int l, const std::string& sched, double* cur, double* other, bool zero);
+    double* sweeps(Level& L, int l, const std::string& sched, double* cur, double* other, bool zero,
+                   size_t done = 0);
     void drop_graph();
     void tune_lanes();
     void make_fp32_copies();

@@ -30,81 +30,211 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kChunk = 512;    // rows per partial sum of the norm kernels
 
+// Row kernels of the CSR levels.  A block takes `rows` consecutive rows (a power
+// of two, at most kBlock): its threads first read the rows' member, class and
+// offsets, one row per thread, and list the rows to work on in LDS; then LPR
+// lanes take a listed row each.  So a half-sweep's lanes are all busy (with LPR
+// lanes per row of either class, those of the other class idled), the per-row
+// data is read once and coalesced, and each lane issues up to kRowLoads<LPR> of
+// its entries' loads together before the first gather of x.
 // VT: type the level's matrix values and 1/a_ii are stored in (double, or
 // float for the optional FP32 coarse levels); vectors and sums stay FP64.
+// Bound by the matrix stream.  Residual of the first coarse level, 64^3, 8
+// directions (7 M rows, 98 M entries, 1.42 GB): 517 -> 385 us (3.7 of the 4.7 TB/s
+// a copy reaches); a warm V(1,1) sweep of 32^3 S8, half of it half-sweeps on
+// these levels: 137 -> 85 ms, where LPR lanes per row of either class, one entry
+// at a time, ran at 2.5 TB/s.
+template <int LPR>
+constexpr int kRowLoads = LPR <= 8 ? 4 : 2;
+
+// Sum over LPR consecutive lanes by DPP moves inside 16 lanes; every lane gets
+// the total.  A fixed tree: reproducible.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true);
+    hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+template <int LPR>
+__device__ __forceinline__ double row_sum(double v) {
+    if constexpr (LPR >= 2) v = dpp_add<0xB1>(v);        // quad_perm [1,0,3,2]
+    if constexpr (LPR >= 4) v = dpp_add<0x4E>(v);        // quad_perm [2,3,0,1]
+    if constexpr (LPR >= 8) v = dpp_add<0x141>(v);       // half-row mirror: the other quad
+    if constexpr (LPR >= 16) v = dpp_add<0x140>(v);      // row mirror: the other half
+    if constexpr (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (LPR >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
+// Row [e0, e0 + len) times x, by LPR lanes (this one: sub).
+template <int LPR, class VT>
+__device__ __forceinline__ double row_dot(const int32_t* __restrict__ col, const VT* __restrict__ val, int64_t e0,
+                                          int len, const double* __restrict__ x, int sub) {
+    constexpr int U = kRowLoads<LPR>;
+    double s = 0.0;
+    for (int q = sub; q < len; q += U * LPR) {
+        int32_t c[U];
+        VT v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + min(q + u * LPR, len - 1);   // past the row: its last entry, not added
+            c[u] = col[e];
+            v[u] = val[e];
+        }
+        double xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double y = s + static_cast<double>(v[u]) * xv[u];
+            s = q + u * LPR < len ? y : s;
+        }
+    }
+    return row_sum<LPR>(s);
+}
+
+// The block's rows with pick(row) set: their numbers in list, offsets of the
+// block's rows (relative to the first) in off; returns how many.
+struct RowBlock {
+    int64_t base, e0;
+    int count;
+};
+template <class Pick>
+__device__ __forceinline__ RowBlock row_block(int64_t n, int rows, const int64_t* __restrict__ rowptr, int* list,
+                                              int* off, Pick&& pick) {
+    __shared__ int s_cnt[kBlock / 64];
+    RowBlock rb;
+    rb.base = static_cast<int64_t>(xcd_block()) * rows;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int64_t row = rb.base + t;
+    const bool in = t < rows && row < n;
+    rb.e0 = rb.base < n ? rowptr[rb.base] : 0;
+    bool on = false;
+    if (in) {
+        const int64_t e = rowptr[row + 1];
+        on = pick(row);
+        off[t + 1] = static_cast<int>(e - rb.e0);
+    }
+    if (t == 0) off[0] = 0;
+    const uint64_t m = __ballot(on);
+    if (lane == 0) s_cnt[wid] = __popcll(m);
+    __syncthreads();
+    int before = 0;
+    rb.count = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+        if (w < wid) before += s_cnt[w];
+        rb.count += s_cnt[w];
+    }
+    if (on) list[before + __popcll(m & ((1ull << lane) - 1ull))] = t;
+    __syncthreads();
+    return rb;
+}
+
+// Half-sweep over the rows of one class: x_i += omega (b_i - (A x)_i) / a_ii;
+// the other class keeps its values.
 template <int LPR, class VT = double>
 __global__ void __launch_bounds__(kBlock)
-k_relax(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+k_relax(int64_t n, int rows, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
         const VT* __restrict__ val, const VT* __restrict__ dinv,
         const int8_t* __restrict__ cf, int8_t which, const uint16_t* __restrict__ seg,
         const uint8_t* __restrict__ active, const uint8_t* __restrict__ relax,
         const double* __restrict__ b, const double* __restrict__ xin, double* __restrict__ xout,
-        double omega, int xin_zero) {
-    const int64_t row = static_cast<int64_t>(xcd_block()) * (kBlock / LPR) + threadIdx.x / LPR;
+        double omega) {
+    __shared__ int list[kBlock], off[kBlock + 1];
+    const RowBlock rb = row_block(n, rows, rowptr, list, off, [&](int64_t row) {
+        const int m = seg[row];
+        const bool mine = cf[row] == which;
+        const double xi = xin[row];
+        if (!(active[m] && relax[m])) return false;
+        if (!mine) xout[row] = xi;
+        return mine;
+    });
     const int sub = threadIdx.x % LPR;
-    if (row >= n) return;
-    const int m = seg[row];
-    if (!(active[m] && relax[m])) return;
-    const double xi = xin_zero ? 0.0 : xin[row];
-    if (cf[row] != which) {
-        if (sub == 0) xout[row] = xi;
-        return;
+    for (int k = threadIdx.x / LPR; k < rb.count; k += kBlock / LPR) {
+        const int i = list[k], e = off[i];
+        const int64_t row = rb.base + i;
+        const double xi = xin[row], bi = b[row], di = static_cast<double>(dinv[row]);
+        const double s = row_dot<LPR, VT>(col, val, rb.e0 + e, off[i + 1] - e, xin, sub);
+        if (sub == 0) xout[row] = xi + omega * (bi - s) * di;
     }
-    double s = 0.0;
-    if (!xin_zero) {
-        for (int64_t e = rowptr[row] + sub; e < rowptr[row + 1]; e += LPR)
-            s += static_cast<double>(val[e]) * xin[col[e]];
-        s = group_sum<LPR>(s);
-    }
-    if (sub == 0) xout[row] = xi + omega * (b[row] - s) * static_cast<double>(dinv[row]);
 }
 
-template <int LPR, class VT = double>
+// The first half-sweep of a schedule from x = 0: x_i = omega b_i / a_ii in its
+// class, 0 in the other.
+template <class VT = double>
 __global__ void __launch_bounds__(kBlock)
-k_residual(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-           const VT* __restrict__ val, const uint16_t* __restrict__ seg,
-           const uint8_t* __restrict__ active, const uint8_t* __restrict__ relax,
-           const double* __restrict__ b, const double* __restrict__ x, double* __restrict__ r) {
-    const int64_t row = static_cast<int64_t>(xcd_block()) * (kBlock / LPR) + threadIdx.x / LPR;
-    const int sub = threadIdx.x % LPR;
-    if (row >= n) return;
-    const int m = seg[row];
-    if (!(active[m] && relax[m])) return;
-    double s = 0.0;
-    for (int64_t e = rowptr[row] + sub; e < rowptr[row + 1]; e += LPR)
-        s += static_cast<double>(val[e]) * x[col[e]];
-    s = group_sum<LPR>(s);
-    if (sub == 0) r[row] = b[row] - s;
-}
-
-// b_c = R r over the rows of the next level (one row per coarse point).
-template <int LPR, class VT = double>
-__global__ void __launch_bounds__(kBlock)
-k_restrict(int64_t nc, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-           const VT* __restrict__ val, const uint16_t* __restrict__ seg_c,
-           const uint8_t* __restrict__ active, const double* __restrict__ r,
-           double* __restrict__ bc) {
-    const int64_t row = static_cast<int64_t>(xcd_block()) * (kBlock / LPR) + threadIdx.x / LPR;
-    const int sub = threadIdx.x % LPR;
-    if (row >= nc) return;
-    if (!active[seg_c[row]]) return;
-    double s = 0.0;
-    for (int64_t e = rowptr[row] + sub; e < rowptr[row + 1]; e += LPR)
-        s += static_cast<double>(val[e]) * r[col[e]];
-    s = group_sum<LPR>(s);
-    if (sub == 0) bc[row] = s;
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_interpolate(int64_t n, const int32_t* __restrict__ p, const uint16_t* __restrict__ seg,
-              const uint8_t* __restrict__ active, const uint8_t* __restrict__ relax,
-              const double* __restrict__ xc, double* __restrict__ x) {
+k_relax_zero(int64_t n, const VT* __restrict__ dinv, const int8_t* __restrict__ cf, int8_t which,
+             const uint16_t* __restrict__ seg, const uint8_t* __restrict__ active,
+             const uint8_t* __restrict__ relax, const double* __restrict__ b, double* __restrict__ xout,
+             double omega) {
     const int64_t row = static_cast<int64_t>(xcd_block()) * kBlock + threadIdx.x;
     if (row >= n) return;
     const int m = seg[row];
     if (!(active[m] && relax[m])) return;
+    xout[row] = cf[row] == which ? omega * b[row] * static_cast<double>(dinv[row]) : 0.0;
+}
+
+template <int LPR, class VT = double>
+__global__ void __launch_bounds__(kBlock)
+k_residual(int64_t n, int rows, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+           const VT* __restrict__ val, const uint16_t* __restrict__ seg,
+           const uint8_t* __restrict__ active, const uint8_t* __restrict__ relax,
+           const double* __restrict__ b, const double* __restrict__ x, double* __restrict__ r) {
+    __shared__ int list[kBlock], off[kBlock + 1];
+    const RowBlock rb = row_block(n, rows, rowptr, list, off, [&](int64_t row) {
+        const int m = seg[row];
+        return active[m] && relax[m];
+    });
+    const int sub = threadIdx.x % LPR;
+    for (int k = threadIdx.x / LPR; k < rb.count; k += kBlock / LPR) {
+        const int i = list[k], e = off[i];
+        const int64_t row = rb.base + i;
+        const double bi = b[row];
+        const double s = row_dot<LPR, VT>(col, val, rb.e0 + e, off[i + 1] - e, x, sub);
+        if (sub == 0) r[row] = bi - s;
+    }
+}
+
+// b_c = R r over the rows of the next level (one row per coarse point), and the
+// first half-sweep of the next level from x = 0 on the rows of the members that
+// relax there (as k_relax_zero; which = 0: x = 0; xc null: no member does).
+template <int LPR, class VT = double>
+__global__ void __launch_bounds__(kBlock)
+k_restrict(int64_t nc, int rows, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+           const VT* __restrict__ val, const uint16_t* __restrict__ seg_c,
+           const uint8_t* __restrict__ active, const double* __restrict__ r,
+           double* __restrict__ bc, const uint8_t* __restrict__ relax_c, const int8_t* __restrict__ cf_c, int8_t which,
+           const VT* __restrict__ dinv_c, double omega, double* __restrict__ xc) {
+    __shared__ int list[kBlock], off[kBlock + 1];
+    const RowBlock rb = row_block(nc, rows, rowptr, list, off, [&](int64_t row) { return active[seg_c[row]] != 0; });
+    const int sub = threadIdx.x % LPR;
+    for (int k = threadIdx.x / LPR; k < rb.count; k += kBlock / LPR) {
+        const int i = list[k], e = off[i];
+        const int64_t row = rb.base + i;
+        const double s = row_dot<LPR, VT>(col, val, rb.e0 + e, off[i + 1] - e, r, sub);
+        if (sub == 0) {
+            bc[row] = s;
+            if (xc && relax_c[seg_c[row]])
+                xc[row] = cf_c[row] == which ? omega * s * static_cast<double>(dinv_c[row]) : 0.0;
+        }
+    }
+}
+
+// xout = xin + P x_c (xin and xout may be the same array).
+__global__ void __launch_bounds__(kBlock)
+k_interpolate(int64_t n, const int32_t* __restrict__ p, const uint16_t* __restrict__ seg,
+              const uint8_t* __restrict__ active, const uint8_t* __restrict__ relax,
+              const double* __restrict__ xc, const double* xin, double* xout) {
+    const int64_t row = static_cast<int64_t>(xcd_block()) * kBlock + threadIdx.x;
+    if (row >= n) return;
+    const int m = seg[row];
     const int32_t c = p[row];
-    if (c >= 0) x[row] += xc[c];
+    const double xi = xin[row];
+    if (!(active[m] && relax[m])) return;
+    if (c >= 0) xout[row] = xi + xc[c];
+    else if (xin != xout) xout[row] = xi;
 }
 
 // x = A^{-1} b on a member's coarsest level (inverse stored column-major).
@@ -1369,13 +1499,13 @@ k_zero_rows(int64_t n, const uint16_t* __restrict__ seg, const uint8_t* __restri
     if (active[m] && relax[m]) x[row] = 0.0;
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_copy_rows(int64_t n, const uint16_t* __restrict__ seg, const uint8_t* __restrict__ active,
-            const uint8_t* __restrict__ relax, const double* __restrict__ src, double* __restrict__ dst) {
-    const int64_t row = static_cast<int64_t>(xcd_block()) * kBlock + threadIdx.x;
-    if (row >= n) return;
-    const int m = seg[row];
-    if (active[m] && relax[m]) dst[row] = src[row];
+// Rows per block of the row kernels: up to kBlock, fewer where that would leave
+// less than about eight blocks per CU (a small level's launch is bound by the
+// rows a block takes one after the other).
+int block_rows(int64_t n, int lpr) {
+    int rows = kBlock / lpr;
+    while (rows < kBlock && n / (2 * rows) >= 2048) rows *= 2;
+    return rows;
 }
 
 template <class F>
@@ -1537,11 +1667,12 @@ void tet_tile_schedule(FineEll& fe, const int32_t* tile_of, const int32_t* tile_
 // returns the buffer holding the result.  `zero`: cur is known to be 0 (the
 // first half-sweep then reads neither the matrix nor cur).
 double* Hierarchy::sweeps(Level& L, int l, const std::string& sched, double* cur, double* other,
-                          bool zero) {
+                          bool zero, size_t done) {
     const int64_t n = L.A.n;
     const uint8_t* act = sv_.active;
     const int kind = l == 0 ? PROF_RELAX_FINE : PROF_RELAX_COARSE;
-    for (char ch : sched) {
+    for (size_t k = done; k < sched.size(); ++k) {
+        const char ch = sched[k];
         const int8_t which = ch == 'F' ? -1 : 1;
         if (ch == 'T' && l == 0 && ell_ && ell_->tet_tiles) {
             const FineEll& E = *ell_;
@@ -1608,20 +1739,27 @@ double* Hierarchy::sweeps(Level& L, int l, const std::string& sched, double* cur
             continue;
         }
         const bool f32 = L.valf.p != nullptr;
-        dispatch_lpr(L.lpr, [&](auto lc) {
-            constexpr int LPR = decltype(lc)::value;
-            const unsigned g = grid_xcd(n, kBlock / LPR);
-            int h = prof_begin(s_, kind);
+        int h = prof_begin(s_, kind);
+        if (zero) {
             if (f32)
-                hipLaunchKernelGGL((k_relax<LPR, float>), dim3(g), dim3(kBlock), 0, s_, n, L.A.rowptr.p,
-                                   L.A.col.p, L.valf.p, L.dinvf.p, L.cf.p, which, L.seg.p, act,
-                                   L.relax.p, L.b.p, cur, other, prm_.omega, zero ? 1 : 0);
+                hipLaunchKernelGGL(k_relax_zero<float>, dim3(grid_xcd(n, kBlock)), dim3(kBlock), 0, s_, n, L.dinvf.p,
+                                   L.cf.p, which, L.seg.p, act, L.relax.p, L.b.p, other, prm_.omega);
             else
-                hipLaunchKernelGGL(k_relax<LPR>, dim3(g), dim3(kBlock), 0, s_, n, L.A.rowptr.p,
-                                   L.A.col.p, L.A.val.p, L.dinv.p, L.cf.p, which, L.seg.p, act,
-                                   L.relax.p, L.b.p, cur, other, prm_.omega, zero ? 1 : 0);
-            prof_end(s_, h, relax_bytes(L, which, zero, f32 ? 4.0 : 8.0));
+                hipLaunchKernelGGL(k_relax_zero<double>, dim3(grid_xcd(n, kBlock)), dim3(kBlock), 0, s_, n, L.dinv.p,
+                                   L.cf.p, which, L.seg.p, act, L.relax.p, L.b.p, other, prm_.omega);
+        } else dispatch_lpr(L.lpr, [&](auto lc) {
+            constexpr int LPR = decltype(lc)::value;
+            const int rows = block_rows(n, LPR);
+            if (f32)
+                hipLaunchKernelGGL((k_relax<LPR, float>), dim3(grid_xcd(n, rows)), dim3(kBlock), 0, s_, n, rows,
+                                   L.A.rowptr.p, L.A.col.p, L.valf.p, L.dinvf.p, L.cf.p, which, L.seg.p, act,
+                                   L.relax.p, L.b.p, cur, other, prm_.omega);
+            else
+                hipLaunchKernelGGL(k_relax<LPR>, dim3(grid_xcd(n, rows)), dim3(kBlock), 0, s_, n, rows,
+                                   L.A.rowptr.p, L.A.col.p, L.A.val.p, L.dinv.p, L.cf.p, which, L.seg.p, act,
+                                   L.relax.p, L.b.p, cur, other, prm_.omega);
         });
+        prof_end(s_, h, relax_bytes(L, which, zero, f32 ? 4.0 : 8.0));
         PAIR_LAUNCH_CHECK();
         std::swap(cur, other);
         zero = false;
@@ -1648,14 +1786,17 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
         }
         if (!has_relax) break;
         const int64_t n = L.A.n;
-        const bool zero = (l == 0) ? x_is_zero : true;
         const std::string& pre = l == 0 ? prm_.relax_pre : prm_.relax_pre_coarse;
-        if (zero && pre.empty()) {
+        if (l == 0 && x_is_zero && pre.empty()) {
             hipLaunchKernelGGL(k_zero_rows, dim3(grid_xcd(n, kBlock)), dim3(kBlock), 0, s_, n, L.seg.p,
                                act, L.relax.p, L.x.p);
             PAIR_LAUNCH_CHECK();
         }
-        cur[l] = sweeps(L, l, pre, L.x.p, L.t.p, zero);
+        // below the finest level the restriction has done the first half-sweep
+        // (from x = 0, into t), or cleared x where the schedule is empty
+        if (l == 0) cur[l] = sweeps(L, l, pre, L.x.p, L.t.p, x_is_zero);
+        else if (pre.empty()) cur[l] = L.x.p;
+        else cur[l] = sweeps(L, l, pre, L.t.p, L.x.p, false, 1);
         if (l == 0 && ell_ && ell_->factored) {
             const FineEll& E = *ell_;
             int h = prof_begin(s_, PROF_RESIDUAL_FINE);
@@ -1675,29 +1816,36 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
             });
         } else dispatch_lpr(L.lpr, [&](auto lc) {
             constexpr int LPR = decltype(lc)::value;
-            const unsigned g = grid_xcd(n, kBlock / LPR);
+            const int rows = block_rows(n, LPR);
+            const unsigned g = grid_xcd(n, rows);
             int h = prof_begin(s_, l == 0 ? PROF_RESIDUAL_FINE : PROF_NKINDS);
             if (L.valf.p)
-                hipLaunchKernelGGL((k_residual<LPR, float>), dim3(g), dim3(kBlock), 0, s_, n, L.A.rowptr.p,
+                hipLaunchKernelGGL((k_residual<LPR, float>), dim3(g), dim3(kBlock), 0, s_, n, rows, L.A.rowptr.p,
                                    L.A.col.p, L.valf.p, L.seg.p, act, L.relax.p, L.b.p, cur[l], L.r.p);
             else
-                hipLaunchKernelGGL(k_residual<LPR>, dim3(g), dim3(kBlock), 0, s_, n, L.A.rowptr.p,
+                hipLaunchKernelGGL(k_residual<LPR>, dim3(g), dim3(kBlock), 0, s_, n, rows, L.A.rowptr.p,
                                    L.A.col.p, L.A.val.p, L.seg.p, act, L.relax.p, L.b.p, cur[l], L.r.p);
             prof_end(s_, h, residual_bytes(L, L.valf.p ? 4.0 : 8.0));
         });
         PAIR_LAUNCH_CHECK();
         Level& C = levels_[l + 1];
+        // with the next level's first half-sweep, where members relax there
+        const bool next_relaxes = l + 2 < nl && C.R.n > 0;
+        const std::string& npre = prm_.relax_pre_coarse;
+        const int8_t first = npre.empty() ? 0 : npre[0] == 'F' ? -1 : 1;
+        double* xc = !next_relaxes ? nullptr : npre.empty() ? C.x.p : C.t.p;
         dispatch_lpr(L.lpr_r, [&](auto lc) {
             constexpr int LPR = decltype(lc)::value;
+            const int rows = block_rows(L.R.n, LPR);
             int h = prof_begin(s_, l == 0 ? PROF_RESTRICT_FINE : PROF_NKINDS);
             if (L.rvalf.p)
-                hipLaunchKernelGGL((k_restrict<LPR, float>), dim3(grid_xcd(L.R.n, kBlock / LPR)), dim3(kBlock),
-                                   0, s_, L.R.n, L.R.rowptr.p, L.R.col.p, L.rvalf.p, C.seg.p, act, L.r.p,
-                                   C.b.p);
+                hipLaunchKernelGGL((k_restrict<LPR, float>), dim3(grid_xcd(L.R.n, rows)), dim3(kBlock), 0, s_,
+                                   L.R.n, rows, L.R.rowptr.p, L.R.col.p, L.rvalf.p, C.seg.p, act, L.r.p, C.b.p,
+                                   C.relax.p, C.cf.p, first, C.dinvf.p, prm_.omega, xc);
             else
-                hipLaunchKernelGGL(k_restrict<LPR>, dim3(grid_xcd(L.R.n, kBlock / LPR)), dim3(kBlock), 0,
-                                   s_, L.R.n, L.R.rowptr.p, L.R.col.p, L.R.val.p, C.seg.p, act, L.r.p,
-                                   C.b.p);
+                hipLaunchKernelGGL(k_restrict<LPR>, dim3(grid_xcd(L.R.n, rows)), dim3(kBlock), 0, s_, L.R.n, rows,
+                                   L.R.rowptr.p, L.R.col.p, L.R.val.p, C.seg.p, act, L.r.p, C.b.p, C.relax.p,
+                                   C.cf.p, first, C.dinv.p, prm_.omega, xc);
             prof_end(s_, h, restrict_bytes(L, L.rvalf.p ? 4.0 : 8.0));
         });
         PAIR_LAUNCH_CHECK();
@@ -1708,17 +1856,14 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
         if (L.R.n == 0) continue;
         Level& C = levels_[l + 1];
         const int64_t n = L.A.n;
-        double* c = cur[l];
+        // into the buffer from which the schedule ends in x
+        const std::string& post = l == 0 ? prm_.relax_post : prm_.relax_post_coarse;
+        double* c = post.size() % 2 == 0 ? L.x.p : L.t.p;
         double* o = c == L.x.p ? L.t.p : L.x.p;
         hipLaunchKernelGGL(k_interpolate, dim3(grid_xcd(n, kBlock)), dim3(kBlock), 0, s_, n, L.p.p,
-                           L.seg.p, act, L.relax.p, C.x.p, c);
+                           L.seg.p, act, L.relax.p, C.x.p, cur[l], c);
         PAIR_LAUNCH_CHECK();
-        double* fin = sweeps(L, l, l == 0 ? prm_.relax_post : prm_.relax_post_coarse, c, o, false);
-        if (fin != L.x.p) {
-            hipLaunchKernelGGL(k_copy_rows, dim3(grid_xcd(n, kBlock)), dim3(kBlock), 0, s_, n, L.seg.p,
-                               act, L.relax.p, fin, L.x.p);
-            PAIR_LAUNCH_CHECK();
-        }
+        sweeps(L, l, post, c, o, false);
     }
 }
 
@@ -1794,8 +1939,9 @@ void Hierarchy::tune_lanes() {
             dispatch_lpr(c, [&](auto lc) {
                 constexpr int LPR = decltype(lc)::value;
                 ms = time_it([&] {
-                    hipLaunchKernelGGL(k_residual<LPR>, dim3(grid_xcd(L.A.n, kBlock / LPR)), dim3(kBlock),
-                                       0, s_, L.A.n, L.A.rowptr.p, L.A.col.p, L.A.val.p, L.seg.p, ones.p,
+                    const int rows = block_rows(L.A.n, LPR);
+                    hipLaunchKernelGGL(k_residual<LPR>, dim3(grid_xcd(L.A.n, rows)), dim3(kBlock),
+                                       0, s_, L.A.n, rows, L.A.rowptr.p, L.A.col.p, L.A.val.p, L.seg.p, ones.p,
                                        L.relax.p, L.b.p, L.x.p, L.r.p);
                 });
             });
@@ -1807,9 +1953,10 @@ void Hierarchy::tune_lanes() {
             dispatch_lpr(c, [&](auto lc) {
                 constexpr int LPR = decltype(lc)::value;
                 ms = time_it([&] {
-                    hipLaunchKernelGGL(k_restrict<LPR>, dim3(grid_xcd(L.R.n, kBlock / LPR)), dim3(kBlock),
-                                       0, s_, L.R.n, L.R.rowptr.p, L.R.col.p, L.R.val.p, C.seg.p, ones.p,
-                                       L.r.p, C.b.p);
+                    const int rows = block_rows(L.R.n, LPR);
+                    hipLaunchKernelGGL(k_restrict<LPR>, dim3(grid_xcd(L.R.n, rows)), dim3(kBlock),
+                                       0, s_, L.R.n, rows, L.R.rowptr.p, L.R.col.p, L.R.val.p, C.seg.p, ones.p,
+                                       L.r.p, C.b.p, C.relax.p, C.cf.p, int8_t(0), C.dinv.p, 0.0, nullptr);
                 });
             });
             if (ms < best) { best = ms; best_r = c; }
