@@ -19,6 +19,7 @@
 // means no flux through the face.
 #include <cmath>
 
+#include "hex_factored.h"
 #include "kernels_common.h"
 #include "transport.h"
 
@@ -349,12 +350,14 @@ k_fine_hex_lanes(int64_t E, int nx, int ny, int nz, const double* __restrict__ r
     const int64_t nel_all = E * B;
     const int64_t g0 = static_cast<int64_t>(blockIdx.x) * (kHexBlock / 8);
     const int64_t gend = g0 + kHexBlock / 8 < nel_all ? g0 + kHexBlock / 8 : nel_all;
-    if (valid)
+    if (dinv) {      // not kept for the factored form, whose right-hand side needs none
+        if (valid)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s_val[threadIdx.x * 8 + c] = Di[c];
-    __syncthreads();
-    for (int64_t q = threadIdx.x; q < (gend - g0) * 64; q += kHexBlock) dinv[g0 * 64 + q] = s_val[q];
-    __syncthreads();
+            for (int c = 0; c < 8; ++c) s_val[threadIdx.x * 8 + c] = Di[c];
+        __syncthreads();
+        for (int64_t q = threadIdx.x; q < (gend - g0) * 64; q += kHexBlock) dinv[g0 * 64 + q] = s_val[q];
+        __syncthreads();
+    }
 
     // inflow faces per axis (constant indices only: no per-thread memory)
     const int64_t nxy = static_cast<int64_t>(nx) * ny;
@@ -685,6 +688,59 @@ k_rhs(int64_t E, int B, const int* __restrict__ dirs, const double* __restrict__
     }
 }
 
+// The scaled right-hand side of a factored batch (FineEll): with D_e = M_e
+// [sigma_t I + T_x (+) T_y (+) T_z], M_e = V (M1 (x) M1 (x) M1), the element source
+// enters as [.]^{-1} (sigma_s phi + q)/(4 pi) without a mass matrix, and dual terms
+// (ext, inflow) as [.]^{-1} M_e^{-1} f, M1^{-1} = [4 -2; -2 4] along each axis.  A
+// thread per element and member (blockIdx.y).  Bound by its stores: it reads no
+// element inverse (512 B per element and member; k_rhs took 358 us for 64^3 and 8
+// directions, this 52 us), so the assembly does not keep them either.
+// DUAL: with ext or inflow terms.
+template <bool DUAL>
+__global__ void __launch_bounds__(128)
+k_rhs_hex(int64_t E, const int* __restrict__ dirs, const double* __restrict__ kap,
+          const int32_t* __restrict__ inflow_side, const double* __restrict__ sigt,
+          const double* __restrict__ sigs, const double* __restrict__ q, const double* __restrict__ phi,
+          const double* __restrict__ ext, int ext_per_dir, const double* __restrict__ inflow,
+          const double* __restrict__ omega, double vol, int nx, int ny, int nz, const double* __restrict__ fref,
+          double* __restrict__ out) {
+    const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (e >= E) return;
+    const int b = blockIdx.y;
+    const int64_t N = E * 8;
+    const HexDir dr = load_hex_dir(static_cast<uint32_t>(b), kap, inflow_side);
+    const double qe = q ? q[e] : 0.0, se = sigs[e];
+    double g[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (phi) load8(phi + e * 8, g);
+#pragma unroll
+    for (int a = 0; a < 8; ++a) g[a] = (se * g[a] + qe) / kFourPi;
+    if constexpr (DUAL) {
+        double f[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        const int m = dirs[b];
+        if (ext) load8(ext + (ext_per_dir ? static_cast<int64_t>(m) * N : 0) + e * 8, f);
+        if (inflow) {
+            const double om[3] = {omega[3 * m], omega[3 * m + 1], omega[3 * m + 2]};
+            double gv[8];
+            load8(inflow + static_cast<int64_t>(m) * N + e * 8, gv);
+            add_inflow<8>(e, om, gv, nx, ny, nz, fref, nullptr, nullptr, f);
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                if ((a >> d) & 1) continue;
+                const double lo = f[a], hi = f[a | (1 << d)];
+                f[a] = 4.0 * lo - 2.0 * hi;
+                f[a | (1 << d)] = 4.0 * hi - 2.0 * lo;
+            }
+#pragma unroll
+        for (int a = 0; a < 8; ++a) g[a] += f[a] / vol;
+    }
+    double y[8];
+    hex_kron_solve(hex_den(sigt[e], dr), dr, g, y);
+    store8(out + static_cast<int64_t>(b) * N + e * 8, y);
+}
+
 // phi_i <- (first ? 0 : phi_i) + sum_b w_b x_b,i in member order (fixed order).
 __global__ void k_phi_accumulate(int64_t N, int B, const double* __restrict__ w,
                                  const double* __restrict__ x, double* __restrict__ phi, int first) {
@@ -830,10 +886,22 @@ void fine_assemble(const DeviceMesh& m, const double* omega_d, const int* dirs_d
     PAIR_CHECK(hb == 0, "singular element block in assembly");
 }
 
-void rhs_kernel(const DeviceMesh& m, int B, const int* dirs_d, const double* dinv,
+void rhs_kernel(const DeviceMesh& m, const FineEll& fe, int B, const int* dirs_d, const double* dinv,
                 const double* sigs, const double* q, const double* phi, const double* ext,
                 bool ext_per_dir, const double* inflow, const double* omega_d, int64_t /*N*/,
                 double* out, hipStream_t s) {
+    if (fe.factored) {
+        const dim3 g(grid_for(m.E, 128), static_cast<unsigned>(B));
+        const double vol = m.h[0] * m.h[1] * m.h[2];
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, g, dim3(128), 0, s, m.E, dirs_d, fe.kap.p, fe.inflow.p, fe.sigt.p, sigs, q, phi,
+                               ext, ext_per_dir ? 1 : 0, inflow, omega_d, vol, m.nx, m.ny, m.nz, m.ref.p + REF_F, out);
+        };
+        if (ext || inflow) launch(k_rhs_hex<true>);
+        else launch(k_rhs_hex<false>);
+        PAIR_LAUNCH_CHECK();
+        return;
+    }
 #define PAIR_RHS_HEX(FLOW)                                                                         \
     hipLaunchKernelGGL((k_rhs<8, FLOW>), dim3(grid_for(m.E * B, 128)), dim3(128), 0, s, m.E, B, dirs_d, \
                        dinv, m.ref.p + REF_M, nullptr, sigs, q, phi, ext, ext_per_dir ? 1 : 0, inflow,    \

@@ -103,7 +103,6 @@ Csr Context::assemble_fine(Batch& bt, hipStream_t s, double* t_assemble_ms) {
     A.rowptr.alloc(A.n + 1);
     A.col.alloc(nnz);
     A.val.alloc(nnz);
-    bt.dinv.alloc(static_cast<size_t>(B) * E * mesh.k * mesh.k);
     bt.ell = std::make_shared<FineEll>();
     FineEll& fe = *bt.ell;
     // factored finest-level operator: structured hexes, every |Omega_d| > tol
@@ -115,6 +114,8 @@ Csr Context::assemble_fine(Batch& bt, hipStream_t s, double* t_assemble_ms) {
                "tile sweeps (T) on hexes need fine_factored = 1 and no direction component of "
                "magnitude <= 1e-12");
     if (tiles && mesh.kind == PAIR_TET4) build_tet_tiles(s);
+    if (fact) bt.dinv.reset();
+    else bt.dinv.alloc(static_cast<size_t>(B) * E * mesh.k * mesh.k);
     fe.E = E;
     std::vector<double> kap;      // host sources of the copies below: kept until the
     std::vector<int32_t> in;      // stream synchronisation at the end of fine_assemble
@@ -247,7 +248,7 @@ void Context::rhs_batch(const Batch& bt, const SourceSpec& src, const double* ph
     const int B = static_cast<int>(bt.dirs.size());
     DBuf<int> dirs_d(B);
     h2d(dirs_d.p, bt.dirs.data(), B, s);
-    rhs_kernel(mesh, B, dirs_d.p, bt.dinv.p, sigs.p, src.q, phi_in, src.ext, src.ext_per_dir,
+    rhs_kernel(mesh, *bt.ell, B, dirs_d.p, bt.dinv.p, sigs.p, src.q, phi_in, src.ext, src.ext_per_dir,
                src.inflow, omega_d.p, N(), out, s);
     PAIR_HIP(hipStreamSynchronize(s));
 }

@@ -43,7 +43,7 @@ struct DeviceMesh {
 // Fine operators of one batch of directions and their AIR hierarchy.
 struct Batch {
     std::vector<int> dirs;                 // directions, in order
-    DBuf<double> dinv;                     // [B][E][k*k] element block inverses
+    DBuf<double> dinv;                     // [B][E][k*k] element block inverses (empty: factored form)
     std::unique_ptr<Hierarchy> H;
     std::shared_ptr<FineEll> ell;          // element-block copy of the finest level
 };
@@ -137,7 +137,7 @@ void fine_counts(const DeviceMesh& m, const double* omega_d, const int* dirs_d, 
 void fine_assemble(const DeviceMesh& m, const double* omega_d, const int* dirs_d, int B,
                    const double* sigt, const int64_t* elem_off, int64_t total_nnz, int64_t* rowptr,
                    int32_t* col, double* val, double* dinv, FineEll& ell, hipStream_t s);
-void rhs_kernel(const DeviceMesh& m, int B, const int* dirs_d, const double* dinv,
+void rhs_kernel(const DeviceMesh& m, const FineEll& fe, int B, const int* dirs_d, const double* dinv,
                 const double* sigs, const double* q, const double* phi, const double* ext,
                 bool ext_per_dir, const double* inflow, const double* omega_d, int64_t N,
                 double* out, hipStream_t s);
