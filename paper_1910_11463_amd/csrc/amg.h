@@ -179,6 +179,12 @@ struct Level {
 // The solve's per-member scratch as plain device pointers: either the
 // hierarchy's own SolveBufs (and finest-level member offsets / counts), or a
 // caller-provided region carved by Hierarchy::carve_solve_scratch.
+// A member's state after a convergence test, in pinned host memory.
+struct MemberResult {
+    double relres, relres0;
+    int iters, active;
+};
+
 struct SolveView {
     double* partial = nullptr;     // [chunks][members] partial sums of the norms
     double* bnorm2 = nullptr;      // per member
@@ -187,7 +193,6 @@ struct SolveView {
     double* relres0 = nullptr;
     int* iters = nullptr;
     uint8_t* active = nullptr;
-    int* n_active = nullptr;       // scalar
     int64_t* moff = nullptr;       // finest-level first row per member
     int64_t* mcnt = nullptr;       // finest-level rows per member
     int chunks = 0;
@@ -200,7 +205,7 @@ struct SolveBufs {
     DBuf<double> relres0;          // per member: first relative residual
     DBuf<int> iters;               // per member
     DBuf<uint8_t> active;          // per member
-    DBuf<int> n_active;            // scalar
+    HBuf<MemberResult> result;     // per member
     int chunks = 0;
 };
 
@@ -237,6 +242,8 @@ public:
     const std::vector<double>& cf_h() const { return cf_h_; }
     double solve_bytes_per_cycle() const;   // algorithmic bytes of one V-cycle (all members)
     double last_solve_bytes() const { return last_bytes_; }
+    const std::vector<int64_t>& level_n0() const { return level_n0_; }
+    const std::vector<int64_t>& level_nnz0() const { return level_nnz0_; }
     int64_t nnz_level(int l) const { return levels_[l].A.nnz; }
     // Use an element-block copy of the finest level for its relaxation,
     // residual and convergence test (its diagonal must be the identity).
@@ -259,6 +266,7 @@ private:
     void drop_graph();
     void tune_lanes();
     void make_fp32_copies();
+    void note_level_sizes();
     void filter_restriction(Level& L, const int32_t* c2f, int64_t nc);
     void residual_norms();
     void launch_cycle_and_test(bool x_is_zero, int it_offset);
@@ -275,8 +283,8 @@ private:
     SolveView sv_;                    // the scratch the solve kernels use
     std::vector<int> iters_h_;
     std::vector<double> relres_h_, cf_h_;
-    std::vector<double> r0_h_;        // host staging of the solve's results,
-    std::vector<uint8_t> act_h_;      // sized at setup
+    // member 0's rows and entries per level
+    std::vector<int64_t> level_n0_, level_nnz0_;
     DBuf<int64_t> moff_d_, mcnt_d_;   // finest-level member offsets / counts
     std::shared_ptr<FineEll> ell_;
     bool finest_identity_ = false;

@@ -341,8 +341,7 @@ void classify(int64_t n, int mode, const int64_t* a, const int64_t* ub,
     hipLaunchKernelGGL(k_classify<NC>, dim3(grid_for(n, 256 * kRowsPT)), dim3(256), 0, s, n, mode, a, ub, rc,
                        cnt.p, mask);
     PAIR_LAUNCH_CHECK();
-    d2h(counts, cnt.p, NC, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(counts, cnt.p, NC, s);
 }
 
 // mask[col[e]] = 1 for every entry (the rows a sparse matrix refers to)
@@ -2691,6 +2690,17 @@ k_gauss_jordan(int nmem, const int64_t* __restrict__ mn, const int64_t* __restri
     }
 }
 
+// Entries of one member's rows on every level: its row offsets' difference.
+constexpr int kMaxLevelEnds = 32;       // options.max_levels <= 32
+struct LevelEnds {
+    int n;
+    const int64_t *first[kMaxLevelEnds], *last[kMaxLevelEnds];
+};
+__global__ void k_level_entries(LevelEnds q, int64_t* __restrict__ out) {
+    const int l = threadIdx.x;
+    if (l < q.n) out[l] = q.first[l] ? *q.last[l] - *q.first[l] : 0;
+}
+
 }  // namespace
 
 // ========================================================================== host
@@ -2751,8 +2761,7 @@ void Hierarchy::coarse_setup(Level& L, const std::vector<int>& members) {
         PAIR_HIP(hipStreamSynchronize(s_));
     }
     int hs = 0;
-    d2h(&hs, sing.p, 1, s_);
-    PAIR_HIP(hipStreamSynchronize(s_));
+    read_back(&hs, sing.p, 1, s_);
     PAIR_CHECK(hs == 0, "singular coarsest-level matrix");
 }
 
@@ -2855,8 +2864,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 cur = nxt;
                 if (round % 3 == 2) {
                     int und = 0;
-                    d2h(&und, pcnt.p + cur, 1, s_);
-                    PAIR_HIP(hipStreamSynchronize(s_));
+                    read_back(&und, pcnt.p + cur, 1, s_);
                     if (und == 0) break;
                     bound = und;
                 }
@@ -2872,8 +2880,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                            d_cnt.p, cidx.p, d_nc.p);
         PAIR_LAUNCH_CHECK();
         std::vector<int64_t> nc(B_);
-        d2h(nc.data(), d_nc.p, B_, s_);
-        PAIR_HIP(hipStreamSynchronize(s_));
+        read_back(nc.data(), d_nc.p, B_, s_);
         std::vector<int64_t> newoff(B_, -1), newcnt(B_, 0);
         int64_t total_c = 0;
         std::vector<int> coarse_here;
@@ -2912,8 +2919,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             hipLaunchKernelGGL(k_cf_counts, dim3(g), dim3(256), 0, s_, n, L.A.rowptr.p, L.cf.p, cc.p);
             PAIR_LAUNCH_CHECK();
             unsigned long long h[4];
-            d2h(h, cc.p, 4, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(h, cc.p, 4, s_);
             L.n_f = static_cast<int64_t>(h[0]);
             L.nnz_f = static_cast<int64_t>(h[1]);
             L.n_c = static_cast<int64_t>(h[2]);
@@ -2985,8 +2991,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             hipLaunchKernelGGL(k_max_row_len, dim3(std::min<int64_t>(grid_for(n, 256), 1024)), dim3(256), 0, s_, n,
                                L.A.rowptr.p, novf.p + 2);
             int maxlen = 0;
-            d2h(&maxlen, novf.p + 2, 1, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(&maxlen, novf.p + 2, 1, s_);
             // the first form: small for rows of at most 15 entries, the wide medium
             // one where rows average more than 40 entries (most of their rows
             // exceed 256 distinct columns), else the medium one
@@ -3005,15 +3010,13 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             // deferred (rcnt = -1) by the next
             nair_launch(nair_form[0], true, static_cast<int>(total_c), nullptr);
             int ovf[5] = {0, 0, 0, 0, 0};
-            d2h(ovf, novf.p, 5, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(ovf, novf.p, 5, s_);
             nair_oseg[1] = ovf[4];
             for (int st = 1; st < 4 && nair_form[st] >= 0 && ovf[3] > 0; ++st) {
                 classify<2>(total_c, 2, nullptr, rcnt.p, {-1}, nair_list[st], nair_nlist[st], s_);
                 PAIR_HIP(hipMemsetAsync(novf.p + 3, 0, sizeof(int), s_));
                 nair_launch(nair_form[st], true, nair_nlist[st][0], nair_list[st][0].p);
-                d2h(ovf, novf.p, 5, s_);
-                PAIR_HIP(hipStreamSynchronize(s_));
+                read_back(ovf, novf.p, 5, s_);
                 nair_oseg[st + 1] = ovf[4];
             }
             for (int st = 1; st < 5; ++st) nair_oseg[st] = std::max(nair_oseg[st], nair_oseg[st - 1]);
@@ -3030,8 +3033,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                                nullptr, nullptr, nullptr, 0, nullptr);
             PAIR_LAUNCH_CHECK();
             int ctl[2] = {0, 0};
-            d2h(ctl, d2ctl.p, 2, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(ctl, d2ctl.p, 2, s_);
             PAIR_CHECK(ctl[0] == 0, "distance-2 lAIR: a local system has more than 512 F points");
             d2ld = std::max(1, ctl[1]);
         } else if (direct)
@@ -3177,8 +3179,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             hipLaunchKernelGGL(k_max_row_len, dim3(grid_for(total_c, 256)), dim3(256), 0, s_, total_c,
                                L.R.rowptr.p, mx.p);
             PAIR_LAUNCH_CHECK();
-            d2h(&r_longest, mx.p, 1, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(&r_longest, mx.p, 1, s_);
         }
 
         // A P: merge the entries of each row of A that interpolate from the same
@@ -3237,8 +3238,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             std::vector<int32_t> rows(lcount[5]);
             d2h(rows.data(), lists[5].p, lcount[5], s_);
             std::vector<int64_t> ubh(total_c);
-            d2h(ubh.data(), ub.p, total_c, s_);
-            PAIR_HIP(hipStreamSynchronize(s_));
+            read_back(ubh.data(), ub.p, total_c, s_);
             gscr_off_h.resize(lcount[5] + 1, 0);
             for (int k = 0; k < lcount[5]; ++k) {
                 int64_t cap = 1;
@@ -3362,7 +3362,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
     sb_.relres0.alloc(B_);
     sb_.iters.alloc(B_);
     sb_.active.alloc(B_);
-    sb_.n_active.alloc(1);
+    sb_.result.alloc(B_);
     int64_t maxcnt = 1;
     for (int b = 0; b < B_; ++b) maxcnt = std::max(maxcnt, levels_[0].cnt[b]);
     sb_.chunks = static_cast<int>((maxcnt + 511) / 512);
@@ -3372,15 +3372,35 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
     h2d(moff_d_.p, levels_[0].off.data(), B_, s_);
     h2d(mcnt_d_.p, levels_[0].cnt.data(), B_, s_);
     sv_ = SolveView{sb_.partial.p, sb_.bnorm2.p, sb_.rnorm2.p, sb_.relres.p, sb_.relres0.p,
-                    sb_.iters.p, sb_.active.p, sb_.n_active.p, moff_d_.p, mcnt_d_.p, sb_.chunks};
+                    sb_.iters.p, sb_.active.p, moff_d_.p, mcnt_d_.p, sb_.chunks};
     iters_h_.assign(B_, 0);
     relres_h_.assign(B_, 0.0);
     cf_h_.assign(B_, 0.0);
-    r0_h_.assign(B_, 0.0);
-    act_h_.assign(B_, 0);
     if (prm_.coarse_fp32) make_fp32_copies();
-    PAIR_HIP(hipStreamSynchronize(s_));
+    note_level_sizes();
     if (prm_.tune) tune_lanes();
+}
+
+// Member 0's rows and entries on every level, read back in one launch (its
+// entries are the difference of two row offsets); synchronises the stream.
+void Hierarchy::note_level_sizes() {
+    const int nl = static_cast<int>(levels_.size());
+    LevelEnds q;
+    q.n = 0;
+    for (int l = 0; l < nl && q.n < kMaxLevelEnds; ++l) {
+        const Level& L = levels_[l];
+        q.first[q.n] = L.off[0] >= 0 ? L.A.rowptr.p + L.off[0] : nullptr;
+        q.last[q.n] = L.off[0] >= 0 ? L.A.rowptr.p + L.off[0] + L.cnt[0] : nullptr;
+        ++q.n;
+    }
+    HBuf<int64_t> out(q.n);
+    hipLaunchKernelGGL(k_level_entries, dim3(1), dim3(64), 0, s_, q, out.p);
+    PAIR_LAUNCH_CHECK();
+    PAIR_HIP(hipStreamSynchronize(s_));
+    level_n0_.assign(q.n, 0);
+    level_nnz0_.assign(out.p, out.p + q.n);
+    for (int l = 0; l < q.n; ++l)
+        if (levels_[l].off[0] >= 0) level_n0_[l] = levels_[l].cnt[0];
 }
 
 void Hierarchy::make_fp32_copies() {

@@ -302,8 +302,9 @@ k_norm_partial(int mode, int chunks, const int64_t* __restrict__ moff,
 }
 
 // mode 0: |b|^2 and initial state.  mode 1: |r|^2, relative residual, cycle
-// count and the active mask of every member; counts members still active.
-// mode 2: initial residual of a nonzero guess.  One block per member; the
+// count and the active mask of every member.  mode 2: initial residual of a
+// nonzero guess.  A member's state also goes to its entry of `result`, which
+// the host reads once the stream is done; a converged member's entry stays.  One block per member; the
 // partial sums are added in a fixed order (strided per thread, then a fixed
 // tree), so the result is reproducible.
 __global__ void __launch_bounds__(256)
@@ -311,7 +312,7 @@ k_norm_finalize(int mode, int B, int chunks, const int64_t* __restrict__ moff,
                 const double* __restrict__ partial, double* __restrict__ bnorm2,
                 double* __restrict__ rnorm2, double* __restrict__ relres,
                 double* __restrict__ relres0, int* __restrict__ iters,
-                uint8_t* __restrict__ active, int* __restrict__ n_active, double tol,
+                uint8_t* __restrict__ active, MemberResult* __restrict__ result, double tol,
                 int max_iter, int x_zero) {
     __shared__ double red[4];
     const int m = blockIdx.x;
@@ -319,6 +320,7 @@ k_norm_finalize(int mode, int B, int chunks, const int64_t* __restrict__ moff,
     if (moff[m] < 0) {
         if (mode == 0 && threadIdx.x == 0) {
             active[m] = 0; iters[m] = 0; relres[m] = 0.0; relres0[m] = 0.0;
+            result[m] = MemberResult{0.0, 0.0, 0, 0};
         }
         return;
     }
@@ -343,6 +345,7 @@ k_norm_finalize(int mode, int B, int chunks, const int64_t* __restrict__ moff,
             relres0[m] = 0.0;
             active[m] = 1;   // mode 2 evaluates the initial guess
         }
+        result[m] = MemberResult{relres[m], relres0[m], 0, active[m]};
         return;
     }
     rnorm2[m] = s;
@@ -353,7 +356,7 @@ k_norm_finalize(int mode, int B, int chunks, const int64_t* __restrict__ moff,
         relres[m] = rel;
         relres0[m] = rel;
         active[m] = (rel > tol) ? 1 : 0;
-        if (active[m]) atomicAdd(n_active, 1);
+        result[m] = MemberResult{rel, rel, iters[m], active[m]};
         return;
     }
     relres[m] = rel;
@@ -361,7 +364,7 @@ k_norm_finalize(int mode, int B, int chunks, const int64_t* __restrict__ moff,
     const bool bad = !(rel == rel) || isinf(rel);
     const bool go = !bad && rel > tol && iters[m] < max_iter;
     active[m] = go ? 1 : 0;
-    if (go) atomicAdd(n_active, 1);
+    result[m] = MemberResult{rel, relres0[m], iters[m], go ? 1 : 0};
 }
 
 // ---------------------------------------------------------------- finest level, element blocks
@@ -1336,8 +1339,6 @@ double tile_relax_bytes(const Level& L, const FineEll& e, int txy, int tz, bool 
     return b;
 }
 
-__global__ void k_zero_int(int* p) { *p = 0; }
-
 __global__ void __launch_bounds__(kBlock)
 k_zero_rows(int64_t n, const uint16_t* __restrict__ seg, const uint8_t* __restrict__ active,
             const uint8_t* __restrict__ relax, double* __restrict__ x) {
@@ -1420,8 +1421,7 @@ static void tet_tile_pack(FineEll& fe, hipStream_t s) {
                        fe.trec.p, fe.tpk.p, fe.tval.p, nout.p);
     PAIR_LAUNCH_CHECK();
     unsigned long long no = 0;
-    d2h(&no, nout.p, 1, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(&no, nout.p, 1, s);
     fe.tout = static_cast<int64_t>(no);
 }
 
@@ -1431,8 +1431,7 @@ static void tet_tile_schedule_cyclic(FineEll& fe, int T, int tmax, hipStream_t s
     std::vector<int32_t> nbr(3 * nel), tof(Em), tptr(T + 1);
     d2h(nbr.data(), fe.nbr.p, 3 * nel, s);
     d2h(tof.data(), fe.tile_of.p, Em, s);
-    d2h(tptr.data(), fe.tile_ptr.p, T + 1, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(tptr.data(), fe.tile_ptr.p, T + 1, s);
     CyclicSchedule cs = tet_schedule_cyclic(nbr, nel, Em, B, T, tof, tptr);
     PAIR_CHECK(!cs.too_large, "tile sweeps: an upwind cycle of more than 16 elements inside a tet tile "
                               "(the exact tile solve holds at most 16 elements of a cycle; use smaller tiles)");
@@ -1474,8 +1473,7 @@ void tet_tile_schedule(FineEll& fe, const int32_t* tile_of, const int32_t* tile_
                        fe.nbr.p, lev.p, flag.p);
     PAIR_LAUNCH_CHECK();
     int hf[2] = {0, 0};
-    d2h(hf, flag.p, 2, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(hf, flag.p, 2, s);
     if (hf[0]) {
         // some tile holds an upwind cycle: the schedule is built on the host with
         // its strongly connected sets
@@ -1833,7 +1831,6 @@ void Hierarchy::set_params(const AmgParams& p) {
 
 void Hierarchy::launch_cycle_and_test(bool x_is_zero, int /*it_offset*/) {
     Level& L0 = levels_[0];
-    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s_, sv_.n_active);
     vcycle_launches(x_is_zero);
     if (ell_ && ell_->factored) {
         const FineEll& E = *ell_;
@@ -1863,7 +1860,7 @@ void Hierarchy::launch_cycle_and_test(bool x_is_zero, int /*it_offset*/) {
     });
     hipLaunchKernelGGL(k_norm_finalize, dim3(B_), dim3(256), 0, s_, 1, B_, sv_.chunks,
                        sv_.moff, sv_.partial, sv_.bnorm2, sv_.rnorm2, sv_.relres,
-                       sv_.relres0, sv_.iters, sv_.active, sv_.n_active, prm_.tol,
+                       sv_.relres0, sv_.iters, sv_.active, sb_.result.p, prm_.tol,
                        prm_.max_iter, 0);
     PAIR_LAUNCH_CHECK();
 }
@@ -1878,7 +1875,7 @@ size_t align_up(size_t b) { return (b + kAlign - 1) / kAlign * kAlign; }
 size_t Hierarchy::solve_scratch_bytes() const {
     const size_t B = static_cast<size_t>(B_);
     return align_up(8 * static_cast<size_t>(sb_.chunks) * B) + 4 * align_up(8 * B) + align_up(4 * B) +
-           align_up(B) + align_up(4) + 2 * align_up(8 * B);
+           align_up(B) + kAlign + 2 * align_up(8 * B);   // kAlign: unused, part of the documented size
 }
 
 SolveView Hierarchy::carve_solve_scratch(void* base) const {
@@ -1898,7 +1895,7 @@ SolveView Hierarchy::carve_solve_scratch(void* base) const {
     v.relres0 = reinterpret_cast<double*>(take(8 * B));
     v.iters = reinterpret_cast<int*>(take(4 * B));
     v.active = reinterpret_cast<uint8_t*>(take(B));
-    v.n_active = reinterpret_cast<int*>(take(4));
+    take(4);
     v.moff = reinterpret_cast<int64_t*>(take(8 * B));
     v.mcnt = reinterpret_cast<int64_t*>(take(8 * B));
     return v;
@@ -1928,7 +1925,6 @@ bool Hierarchy::solve_in(void* scratch, bool x_is_zero) {
 bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
     Level& L0 = levels_[0];
     // |b| per member and the initial state
-    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s_, sv_.n_active);
     dispatch_lpr(L0.lpr, [&](auto lc) {
         constexpr int LPR = decltype(lc)::value;
         hipLaunchKernelGGL(k_norm_partial<LPR>, dim3(sv_.chunks, B_), dim3(kBlock), 0, s_, 0,
@@ -1937,7 +1933,7 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
     });
     hipLaunchKernelGGL(k_norm_finalize, dim3(B_), dim3(256), 0, s_, 0, B_, sv_.chunks,
                        sv_.moff, sv_.partial, sv_.bnorm2, sv_.rnorm2, sv_.relres,
-                       sv_.relres0, sv_.iters, sv_.active, sv_.n_active, prm_.tol,
+                       sv_.relres0, sv_.iters, sv_.active, sb_.result.p, prm_.tol,
                        prm_.max_iter, x_is_zero ? 1 : 0);
     PAIR_LAUNCH_CHECK();
     if (!x_is_zero) {
@@ -1949,17 +1945,23 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
         });
         hipLaunchKernelGGL(k_norm_finalize, dim3(B_), dim3(256), 0, s_, 2, B_,
                            sv_.chunks, sv_.moff, sv_.partial, sv_.bnorm2, sv_.rnorm2,
-                           sv_.relres, sv_.relres0, sv_.iters, sv_.active, sv_.n_active,
+                           sv_.relres, sv_.relres0, sv_.iters, sv_.active, sb_.result.p,
                            prm_.tol, prm_.max_iter, 0);
         PAIR_LAUNCH_CHECK();
     } else {
         // x = 0 exactly on entry: members with b = 0 are done (x = 0 is exact)
         PAIR_HIP(hipMemsetAsync(L0.x.p, 0, L0.A.n * sizeof(double), s_));
     }
-    d2h(act_h_.data(), sv_.active, B_, s_);
-    PAIR_HIP(hipStreamSynchronize(s_));
-    int n_act = 0;
-    for (auto a : act_h_) n_act += a;
+    // members still active, once the stream is done
+    auto wait = [&] {
+        PAIR_HIP(hipStreamSynchronize(s_));
+        int n = 0;
+        for (int b = 0; b < B_; ++b) n += sb_.result.p[b].active;
+        return n;
+    };
+    // from x = 0 every member with b != 0 needs a cycle, so the first one is
+    // launched without looking (a cycle with no active member changes nothing)
+    int n_act = x_is_zero ? 1 : wait();
 
     int cycles = 0;
     bool first = true;
@@ -1983,23 +1985,23 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
         }
         first = false;
         ++cycles;
-        d2h(&n_act, sv_.n_active, 1, s_);
-        PAIR_HIP(hipStreamSynchronize(s_));
+        n_act = wait();
     }
-    last_bytes_ = cycles * solve_bytes_per_cycle();
     // per-member results (host vectors sized at setup: assign does not reallocate)
-    d2h(iters_h_.data(), sv_.iters, B_, s_);
-    d2h(relres_h_.data(), sv_.relres, B_, s_);
-    d2h(r0_h_.data(), sv_.relres0, B_, s_);
-    PAIR_HIP(hipStreamSynchronize(s_));
     std::fill(cf_h_.begin(), cf_h_.end(), 0.0);
     bool ok = true;
+    int most = 0;
     for (int b = 0; b < B_; ++b) {
+        const MemberResult& r = sb_.result.p[b];
+        iters_h_[b] = r.iters;
+        relres_h_[b] = r.relres;
+        most = std::max(most, r.iters);
         if (L0.off[b] < 0) continue;
-        if (iters_h_[b] > 0 && r0_h_[b] > 0.0 && relres_h_[b] > 0.0)
-            cf_h_[b] = std::pow(relres_h_[b] / r0_h_[b], 1.0 / iters_h_[b]);
+        if (iters_h_[b] > 0 && r.relres0 > 0.0 && relres_h_[b] > 0.0)
+            cf_h_[b] = std::pow(relres_h_[b] / r.relres0, 1.0 / iters_h_[b]);
         if (!prm_.fixed_cycles && !(relres_h_[b] <= prm_.tol)) ok = false;
     }
+    last_bytes_ = most * solve_bytes_per_cycle();
     return ok;
 }
 

@@ -545,7 +545,8 @@ static int solve_impl(Context& c, int mode, const SourceSpec& src, const double*
                       DBuf<double>& psi_buf, DBuf<double>& phi_buf, pair_stats* st) {
     const int64_t N = c.N();
     if (!psi_buf.p || psi_buf.n != static_cast<size_t>(c.M) * N) psi_buf.alloc(static_cast<size_t>(c.M) * N);
-    DBuf<double> prev(N), cur(N), nrm(2);
+    DBuf<double> prev(N), cur(N);
+    if (!c.norms.p) c.norms.alloc(2);
     if (phi0_dev) d2d(prev.p, phi0_dev, N, c.s);
     else PAIR_HIP(hipMemsetAsync(prev.p, 0, N * sizeof(double), c.s));
     int rc = PAIR_OK;
@@ -556,11 +557,8 @@ static int solve_impl(Context& c, int mode, const SourceSpec& src, const double*
         bool ok = c.sweep(mode, src, prev.p, psi_buf.p, cur.p, st, c.opt.warm_start && it > 1);
         inner_ok = inner_ok && ok;
         c.psi_valid = true;
-        diff_norms(N, cur.p, prev.p, nrm.p, c.s);
-        double hn[2];
-        d2h(hn, nrm.p, 2, c.s);
-        PAIR_HIP(hipStreamSynchronize(c.s));
-        const double d = std::sqrt(hn[0]), a = std::sqrt(hn[1]);
+        diff_norms(N, cur.p, prev.p, c.norms.p, c.s);
+        const double d = std::sqrt(c.norms.p[0]), a = std::sqrt(c.norms.p[1]);
         rel = a > 0.0 ? d / a : d;
         std::swap(prev, cur);
         bool stop;

@@ -773,11 +773,18 @@ k_diff_partial(int64_t N, const double* __restrict__ a, const double* __restrict
     }
 }
 
-__global__ void k_diff_final(const double* __restrict__ partial, double* __restrict__ out) {
-    double d = 0.0, a = 0.0;
-    for (int i = 0; i < kRedBlocks; ++i) { d += partial[2 * i]; a += partial[2 * i + 1]; }
-    out[0] = d;
-    out[1] = a;
+// One block; out2 in pinned host memory.
+__global__ void __launch_bounds__(kRedBlocks)
+k_diff_final(const double* __restrict__ partial, double* __restrict__ out) {
+    __shared__ double s0[kRedBlocks / 64], s1[kRedBlocks / 64];
+    const double d = group_sum<64>(partial[2 * threadIdx.x]), a = group_sum<64>(partial[2 * threadIdx.x + 1]);
+    if ((threadIdx.x & 63) == 0) { s0[threadIdx.x >> 6] = d; s1[threadIdx.x >> 6] = a; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double td = 0.0, ta = 0.0;
+    for (int w = 0; w < kRedBlocks / 64; ++w) { td += s0[w]; ta += s1[w]; }
+    out[0] = td;
+    out[1] = ta;
 }
 
 // dJ/dsigma_t,e = -sum_m w_m x_{m,e}^T M_e psi_{m,e},  x_m = psi_adj[refl[m]];
@@ -840,8 +847,7 @@ void tet_geometry(DeviceMesh& m, int64_t /*n_vert*/, hipStream_t s) {
                        m.ev.p, m.nbr.p, m.unode.p, m.nvec.p, m.mass.p, m.vol.p, bad.p);
     PAIR_LAUNCH_CHECK();
     int hb = 0;
-    d2h(&hb, bad.p, 1, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(&hb, bad.p, 1, s);
     PAIR_CHECK(hb == 0, std::to_string(hb) + " tetrahedra have zero volume");
 }
 
@@ -881,8 +887,7 @@ void fine_assemble(const DeviceMesh& m, const double* omega_d, const int* dirs_d
     hipLaunchKernelGGL(k_set_last, dim3(1), dim3(1), 0, s, rowptr, nrows, total_nnz);
     PAIR_LAUNCH_CHECK();
     int hb = 0;
-    d2h(&hb, bad.p, 1, s);
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(&hb, bad.p, 1, s);
     PAIR_CHECK(hb == 0, "singular element block in assembly");
 }
 
@@ -932,7 +937,7 @@ void phi_accumulate(int64_t N, int B, const double* w_batch_d, const double* x, 
 void diff_norms(int64_t N, const double* a, const double* b, double* out2, hipStream_t s) {
     DBuf<double> part(2 * kRedBlocks);
     hipLaunchKernelGGL(k_diff_partial, dim3(kRedBlocks), dim3(256), 0, s, N, a, b, part.p);
-    hipLaunchKernelGGL(k_diff_final, dim3(1), dim3(1), 0, s, part.p, out2);
+    hipLaunchKernelGGL(k_diff_final, dim3(1), dim3(kRedBlocks), 0, s, part.p, out2);
     PAIR_LAUNCH_CHECK();
     PAIR_HIP(hipStreamSynchronize(s));
 }

@@ -108,6 +108,44 @@ inline void d2d(T* dst, const T* src, size_t n, hipStream_t s) {
     if (n) PAIR_HIP(hipMemcpyAsync(dst, src, n * sizeof(T), hipMemcpyDeviceToDevice, s));
 }
 
+// Pinned host memory that kernels write results to (a device copy into pageable
+// memory costs 12 us over the kernel and the wait for it, a store to a pinned
+// page nothing measurable).  Freed blocks are kept for the next owner and given
+// back by pool_release_all(); an owner frees its block only after the kernels
+// that write it are done.
+void* pinned_alloc(size_t bytes);
+void pinned_free(void* p);
+
+template <class T>
+struct HBuf {
+    T* p = nullptr;
+    size_t n = 0;
+    HBuf() = default;
+    explicit HBuf(size_t count) { alloc(count); }
+    HBuf(const HBuf&) = delete;
+    HBuf& operator=(const HBuf&) = delete;
+    ~HBuf() { reset(); }
+    void alloc(size_t count) {
+        reset();
+        n = count;
+        if (count) p = static_cast<T*>(pinned_alloc(count * sizeof(T)));
+    }
+    void reset() {
+        if (p) pinned_free(p);
+        p = nullptr;
+        n = 0;
+    }
+};
+
+// Copies n values to the host through pinned memory and waits for the stream.
+template <class T>
+inline void read_back(T* h, const T* d, size_t n, hipStream_t s) {
+    HBuf<T> pin(n);
+    if (n) PAIR_HIP(hipMemcpyAsync(pin.p, d, n * sizeof(T), hipMemcpyDeviceToHost, s));
+    PAIR_HIP(hipStreamSynchronize(s));
+    for (size_t i = 0; i < n; ++i) h[i] = pin.p[i];
+}
+
 inline unsigned grid_for(int64_t n, int block) {
     int64_t g = (n + block - 1) / block;
     if (g < 1) g = 1;

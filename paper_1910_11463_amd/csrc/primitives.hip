@@ -1,4 +1,5 @@
 // Device primitives: caching allocator, exclusive scan, member-id fill.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -19,6 +20,8 @@ struct Pool {
     std::multimap<std::pair<hipStream_t, size_t>, void*> free_blocks;   // (stream, size) -> ptr
     std::unordered_map<void*, Block> live;
     size_t in_use = 0;
+    std::multimap<size_t, void*> pinned_free;       // size -> ptr
+    std::unordered_map<void*, size_t> pinned_live;
 };
 Pool& pool() {
     static Pool* p = new Pool();   // intentionally leaked: outlives static destructors
@@ -103,6 +106,35 @@ void pool_release_all() {
     std::lock_guard<std::mutex> g(P.mu);
     for (auto& kv : P.free_blocks) (void)hipFree(kv.second);
     P.free_blocks.clear();
+    for (auto& kv : P.pinned_free) (void)hipHostFree(kv.second);
+    P.pinned_free.clear();
+}
+
+void* pinned_alloc(size_t bytes) {
+    Pool& P = pool();
+    const size_t sz = std::max<size_t>(4096, round_size(bytes));
+    std::lock_guard<std::mutex> g(P.mu);
+    auto it = P.pinned_free.find(sz);
+    void* p = nullptr;
+    if (it != P.pinned_free.end()) {
+        p = it->second;
+        P.pinned_free.erase(it);
+    } else if (hipHostMalloc(&p, sz, hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        throw Error(E_OOM, "pinned host allocation of " + std::to_string(sz) + " bytes failed");
+    }
+    P.pinned_live[p] = sz;
+    return p;
+}
+
+void pinned_free(void* p) {
+    if (!p) return;
+    Pool& P = pool();
+    std::lock_guard<std::mutex> g(P.mu);
+    auto it = P.pinned_live.find(p);
+    if (it == P.pinned_live.end()) return;
+    P.pinned_free.emplace(it->second, p);
+    P.pinned_live.erase(it);
 }
 
 size_t pool_bytes_in_use() { return pool().in_use; }
@@ -181,8 +213,7 @@ int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s
     hipLaunchKernelGGL(k_set_total, dim3(1), dim3(1), 0, s, out, n, in + (n - 1), out + (n - 1));
     PAIR_LAUNCH_CHECK();
     int64_t total = 0;
-    PAIR_HIP(hipMemcpyAsync(&total, out + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    PAIR_HIP(hipStreamSynchronize(s));
+    read_back(&total, out + n, 1, s);
     return total;
 }
 

@@ -24,6 +24,7 @@ double now_ms() {
 
 Context::~Context() {
     batches.clear();
+    for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (acc_stream) worker_streams.push_back(acc_stream);
     for (hipStream_t w : worker_streams) {
         (void)hipStreamSynchronize(w);
@@ -91,7 +92,8 @@ Csr Context::assemble_fine(Batch& bt, hipStream_t s, double* t_assemble_ms) {
     const int64_t E = mesh.E, N = this->N();
     double t0 = now_ms();
     PAIR_CHECK(N * B < (int64_t(1) << 31), "batch too large for int32 column indices; lower batch_size");
-    DBuf<int> dirs_d(B);
+    DBuf<int>& dirs_d = bt.dirs_d;
+    dirs_d.alloc(B);
     h2d(dirs_d.p, bt.dirs.data(), B, s);
     DBuf<int64_t> cnt(E * B), eoff(E * B + 1);
     fine_counts(mesh, omega_d.p, dirs_d.p, B, cnt.p, s);
@@ -246,11 +248,8 @@ void Context::build_batches(int mode, pair_stats* st) {
 void Context::rhs_batch(const Batch& bt, const SourceSpec& src, const double* phi_in, double* out,
                         hipStream_t s) {
     const int B = static_cast<int>(bt.dirs.size());
-    DBuf<int> dirs_d(B);
-    h2d(dirs_d.p, bt.dirs.data(), B, s);
-    rhs_kernel(mesh, *bt.ell, B, dirs_d.p, bt.dinv.p, sigs.p, src.q, phi_in, src.ext, src.ext_per_dir,
+    rhs_kernel(mesh, *bt.ell, B, bt.dirs_d.p, bt.dinv.p, sigs.p, src.q, phi_in, src.ext, src.ext_per_dir,
                src.inflow, omega_d.p, N(), out, s);
-    PAIR_HIP(hipStreamSynchronize(s));
 }
 
 // Batches run in turn on one stream, or (options.streams > 1) batch i on
@@ -287,10 +286,13 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
     std::exception_ptr first_error;
     bool all_ok = true;
     double t_asm = 0.0, t_setup = 0.0, t_solve = 0.0, t_other = 0.0, bytes = 0.0;
-    hipEvent_t ready = nullptr;
-    std::vector<hipEvent_t> ev(2 * static_cast<size_t>(std::max(L, 1)), nullptr);   // per worker
-    PAIR_HIP(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
-    for (auto& e : ev) PAIR_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    while (events.size() < 1 + 2 * static_cast<size_t>(std::max(L, 1))) {
+        hipEvent_t e = nullptr;
+        PAIR_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        events.push_back(e);
+    }
+    const hipEvent_t ready = events[0];
+    const hipEvent_t* const ev = events.data() + 1;   // two per worker
     PAIR_HIP(hipEventRecord(ready, s));   // work queued before the sweep (phi_in, psi)
     const hipStream_t acc_s = L > 1 ? acc_stream : nullptr;
     if (acc_s) PAIR_HIP(hipStreamWaitEvent(acc_s, ready, 0));
@@ -302,20 +304,10 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
             Hierarchy& H = *bt.H;
             if (i == 0) {
                 // member 0 of batch 0 is direction 0: its rows and entries per level
-                const int nl = std::min(H.num_levels(), PAIR_MAX_LEVELS);
-                std::vector<int64_t> ends(2 * static_cast<size_t>(nl), 0);
-                const hipStream_t hs = batch_stream(i);
+                const int nl = std::min(static_cast<int>(H.level_n0().size()), PAIR_MAX_LEVELS);
                 for (int l = 0; l < nl; ++l) {
-                    Level& Lv = H.level(l);
-                    if (Lv.off[0] < 0) continue;
-                    d2h(&ends[2 * l], Lv.A.rowptr.p + Lv.off[0], 1, hs);
-                    d2h(&ends[2 * l + 1], Lv.A.rowptr.p + Lv.off[0] + Lv.cnt[0], 1, hs);
-                }
-                PAIR_HIP(hipStreamSynchronize(hs));
-                for (int l = 0; l < nl; ++l) {
-                    Level& Lv = H.level(l);
-                    st->level_n[l] = Lv.off[0] >= 0 ? Lv.cnt[0] : 0;
-                    st->level_nnz[l] = Lv.off[0] >= 0 ? ends[2 * l + 1] - ends[2 * l] : 0;
+                    st->level_n[l] = H.level_n0()[l];
+                    st->level_nnz[l] = H.level_nnz0()[l];
                 }
             }
             for (int b = 0; b < H.members(); ++b) st->levels_max = std::max(st->levels_max, H.member_levels(b));
@@ -347,8 +339,7 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
         const double t1 = now_ms();
         rhs_batch(bt, src, phi_in, bt.H->b0(), ss);
         double* x0 = bt.H->x0();
-        if (use_warm)
-            for (int b = 0; b < B; ++b) d2d(x0 + b * N, psi.p + static_cast<int64_t>(bt.dirs[b]) * N, N, ss);
+        if (use_warm) d2d(x0, psi.p + static_cast<int64_t>(bt.dirs.front()) * N, static_cast<int64_t>(B) * N, ss);
         const double t2 = now_ms();
         bool ok;
         {
@@ -361,11 +352,11 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
             dir_iters[m] = bt.H->iters_h()[b];
             dir_cf[m] = bt.H->cf_h()[b];
             dir_relres[m] = bt.H->relres_h()[b];
-            if (psi_out) d2d(psi_out + static_cast<int64_t>(m) * N, x0 + b * N, N, ss);
         }
+        // the members of a batch are consecutive directions
+        PAIR_CHECK(bt.dirs.back() - bt.dirs.front() == B - 1, "batch directions not consecutive");
+        if (psi_out) d2d(psi_out + static_cast<int64_t>(bt.dirs.front()) * N, x0, static_cast<int64_t>(B) * N, ss);
         if (phi_out) {
-            // the members of a batch are consecutive directions
-            PAIR_CHECK(bt.dirs.back() - bt.dirs.front() == B - 1, "batch directions not consecutive");
             const double* wbd = w_d.p + bt.dirs.front();
             std::unique_lock<std::mutex> lk(mu);
             cv.wait(lk, [&] { return turn == i || failed; });
@@ -426,8 +417,6 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
         for (int w = 0; w < L; ++w) (void)hipStreamSynchronize(batch_stream(static_cast<size_t>(w)));
         (void)hipStreamSynchronize(acc_s);
     }
-    (void)hipEventDestroy(ready);
-    for (auto e : ev) (void)hipEventDestroy(e);
     if (first_error) {
         cached_mode = -1;
         batches.clear();

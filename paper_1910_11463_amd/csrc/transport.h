@@ -43,6 +43,7 @@ struct DeviceMesh {
 // Fine operators of one batch of directions and their AIR hierarchy.
 struct Batch {
     std::vector<int> dirs;                 // directions, in order
+    DBuf<int> dirs_d;                      // the same on the device
     DBuf<double> dinv;                     // [B][E][k*k] element block inverses (empty: factored form)
     std::unique_ptr<Hierarchy> H;
     std::shared_ptr<FineEll> ell;          // element-block copy of the finest level
@@ -96,11 +97,14 @@ struct Context {
     hipStream_t acc_stream = nullptr;          // scalar-flux sums of concurrent batches
     std::shared_ptr<TuneCache> tune_cache = std::make_shared<TuneCache>();
     int cached_mode = -1;
+    // events of a sweep: [0] its start, then two per worker stream
+    std::vector<hipEvent_t> events;
 
     // state
     DBuf<double> psi;                   // [M][N] last angular flux
     bool psi_valid = false;
     DBuf<double> phi;                   // [N] last scalar flux
+    HBuf<double> norms;                 // |dphi|^2, |phi|^2 of the last source iteration
     std::vector<int> dir_iters;
     std::vector<double> dir_cf, dir_relres;
 
@@ -143,6 +147,7 @@ void rhs_kernel(const DeviceMesh& m, const FineEll& fe, int B, const int* dirs_d
                 double* out, hipStream_t s);
 void phi_accumulate(int64_t N, int B, const double* w_batch_d, const double* x, double* phi,
                     bool first, hipStream_t s);
+// out2: pinned host memory; synchronises the stream
 void diff_norms(int64_t N, const double* a, const double* b, double* out2, hipStream_t s);
 void adjoint_contract(const DeviceMesh& m, int M, const double* w_d, const int* refl_d,
                       const double* psi, const double* psi_adj, const double* phi,
