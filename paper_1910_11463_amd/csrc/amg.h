@@ -258,7 +258,7 @@ public:
     void set_params(const AmgParams& p);
 
 private:
-    void build_level_aux(Level& L, int l);
+    void build_level_aux(Level& L, int l, const int64_t* off_d, const int64_t* cnt_d);
     void coarse_setup(Level& L, const std::vector<int>& members);
     void vcycle_launches(bool x_is_zero);
     double* sweeps(Level& L, int l, const std::string& sched, double* cur, double* other, bool zero,
@@ -307,9 +307,10 @@ public:
 // Exclusive scan of n int64 counts into out[0..n] (out[n] = total); returns total.
 int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
 
-// Member id per row from member row offsets.
-void fill_segments(uint16_t* seg, int64_t n, const std::vector<int64_t>& off,
-                   const std::vector<int64_t>& cnt, hipStream_t s);
+// Member id per row from the members' first rows (-1: absent) and rows on the
+// device; most: the largest member's rows.
+void fill_segments(uint16_t* seg, int members, int64_t most, const int64_t* off_d, const int64_t* cnt_d,
+                   hipStream_t s);
 
 int choose_lpr(double avg_nnz_per_row);
 

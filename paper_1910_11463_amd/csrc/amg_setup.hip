@@ -2705,11 +2705,11 @@ __global__ void k_level_entries(LevelEnds q, int64_t* __restrict__ out) {
 
 // ========================================================================== host
 
-void Hierarchy::build_level_aux(Level& L, int l) {
+void Hierarchy::build_level_aux(Level& L, int l, const int64_t* off_d, const int64_t* cnt_d) {
     const int64_t n = L.A.n;
     L.dinv.alloc(n);
     L.seg.alloc(n);
-    fill_segments(L.seg.p, n, L.off, L.cnt, s_);
+    fill_segments(L.seg.p, B_, *std::max_element(L.cnt.begin(), L.cnt.end()), off_d, cnt_d, s_);
     L.x.alloc(n);
     L.t.alloc(n);
     L.b.alloc(n);
@@ -2784,7 +2784,9 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
 
     for (int l = 0;; ++l) {
         Level& L = levels_[l];
-        build_level_aux(L, l);
+        h2d(d_off.p, L.off.data(), B_, s_);
+        h2d(d_cnt.p, L.cnt.data(), B_, s_);
+        build_level_aux(L, l, d_off.p, d_cnt.p);
         const int64_t n = L.A.n;
         // members that coarsen further
         std::vector<uint8_t> part(B_, 0);
@@ -2810,8 +2812,6 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             break;
         }
         h2d(d_part.p, part.data(), B_, s_);
-        h2d(d_off.p, L.off.data(), B_, s_);
-        h2d(d_cnt.p, L.cnt.data(), B_, s_);
 
         // strength + lambda (fused with 1/a_ii)
         DBuf<uint8_t> sflag(L.A.nnz);

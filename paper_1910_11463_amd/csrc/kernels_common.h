@@ -52,6 +52,49 @@ __device__ __forceinline__ double group_max(double v) {
     return v;
 }
 
+// Exclusive prefix of one tile's total over the tiles before it, in one pass over
+// the data (decoupled look-back; Merrill and Garland 2016): every tile publishes
+// its total and then its inclusive prefix in `status` (zero before the launch),
+// value << 2 | state (0 nothing, 1 total, 2 inclusive prefix).  Tiles are numbered
+// by tile_ticket, in the order in which their blocks start, so the tiles a block
+// waits for are running or done, and each publishes its total before it waits:
+// every wait ends.  Call with one whole wave; every lane gets the prefix.
+// Values below 2^61.
+__device__ __forceinline__ int64_t tile_prefix(unsigned long long* status, int64_t tile, int64_t total) {
+    const int lane = threadIdx.x & 63;
+    auto put = [&](unsigned long long w) {
+        if (lane == 0) __hip_atomic_store(&status[tile], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    int64_t before = 0;
+    if (tile > 0) {
+        put(static_cast<unsigned long long>(total) << 2 | 1ull);
+        for (int64_t last = tile - 1;; last -= 64) {
+            const int64_t i = last - lane;
+            unsigned long long w = 2ull;         // before the first tile: prefix 0
+            if (i >= 0)
+                do {
+                    w = __hip_atomic_load(&status[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } while ((w & 3ull) == 0);
+            const uint64_t full = __ballot((w & 3ull) == 2ull);
+            const int stop = full ? __ffsll(static_cast<unsigned long long>(full)) - 1 : 63;
+            int64_t v = lane <= stop ? static_cast<int64_t>(w >> 2) : 0;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+            before += v;
+            if (full) break;
+        }
+    }
+    put(static_cast<unsigned long long>(before + total) << 2 | 2ull);
+    return before;
+}
+
+// The calling block's tile number (all threads; shared storage of the caller).
+__device__ __forceinline__ int64_t tile_ticket(unsigned* counter, unsigned* shared) {
+    if (threadIdx.x == 0) *shared = atomicAdd(counter, 1u);
+    __syncthreads();
+    return *shared;
+}
+
 // Append to a global list with one atomic per block: every thread of the
 // one-dimensional NT-thread block must call this.  Returns the slot of the
 // calling thread, or -1.  The order of entries across blocks is not fixed.

@@ -145,14 +145,22 @@ constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
+// One pass: a tile's values through LDS, its prefix by look-back.  status:
+// ntiles words and the ticket, zero on entry.  The last tile writes the total to
+// out[n] and to the host page.  Bound by its loads and stores (16 B per value);
+// a pass for the tiles' sums, one for their offsets and a wait per level before:
+// 14 M values 3 launches and 2 waits, now one each.
 __global__ void __launch_bounds__(kScanBlock)
-k_scan_tiles(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t n,
-             int64_t* __restrict__ tile_sums) {
+k_scan(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t n, int64_t ntiles,
+       unsigned long long* __restrict__ status, int64_t* __restrict__ host_total) {
     __shared__ int64_t sh[kScanTile];
     __shared__ int64_t wsum[kScanBlock / 64];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile;
+    __shared__ int64_t s_before;
+    __shared__ unsigned s_tile;
+    const int64_t tile = tile_ticket(reinterpret_cast<unsigned*>(status + ntiles), &s_tile);
+    const int64_t base = tile * kScanTile;
     for (int i = threadIdx.x; i < kScanTile; i += kScanBlock) {
-        int64_t g = base + i;
+        const int64_t g = base + i;
         sh[i] = g < n ? in[g] : 0;
     }
     __syncthreads();
@@ -165,30 +173,33 @@ k_scan_tiles(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t 
     }
     // exclusive scan of the per-thread totals across the block
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int64_t incl = wave_inclusive_scan(run);
+    const int64_t incl = wave_inclusive_scan(run);
     if (lane == 63) wsum[wid] = incl;
     __syncthreads();
-    int64_t woff = 0;
-    for (int w = 0; w < wid; ++w) woff += wsum[w];
-    int64_t excl = woff + incl - run;
+    int64_t woff = 0, total = 0;
+    for (int w = 0; w < kScanBlock / 64; ++w) {
+        if (w < wid) woff += wsum[w];
+        total += wsum[w];
+    }
+    if (wid == 0) {
+        const int64_t before = tile_prefix(status, tile, total);
+        if (lane == 0) {
+            s_before = before;
+            if (tile == ntiles - 1) {
+                out[n] = before + total;
+                *host_total = before + total;
+            }
+        }
+    }
+    __syncthreads();
+    const int64_t excl = s_before + woff + incl - run;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) sh[threadIdx.x * kScanItems + k] = v[k] + excl;
     __syncthreads();
     for (int i = threadIdx.x; i < kScanTile; i += kScanBlock) {
-        int64_t g = base + i;
+        const int64_t g = base + i;
         if (g < n) out[g] = sh[i];
     }
-    if (threadIdx.x == kScanBlock - 1) tile_sums[blockIdx.x] = excl + run;
-}
-
-__global__ void k_add_tile_offsets(int64_t* __restrict__ out, int64_t n,
-                                   const int64_t* __restrict__ off) {
-    int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g < n) out[g] += off[g / kScanTile];
-}
-
-__global__ void k_set_total(int64_t* out, int64_t n, const int64_t* in_last, const int64_t* out_last) {
-    out[n] = (n > 0) ? (*out_last + *in_last) : 0;
 }
 }  // namespace
 
@@ -199,41 +210,37 @@ int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s
         PAIR_HIP(hipStreamSynchronize(s));
         return 0;
     }
-    int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    DBuf<int64_t> sums(ntiles), offs(ntiles + 1);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(static_cast<unsigned>(ntiles)), dim3(kScanBlock), 0, s,
-                       in, out, n, sums.p);
+    const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
+    DBuf<unsigned long long> status(ntiles + 1);
+    HBuf<int64_t> total(1);
+    PAIR_HIP(hipMemsetAsync(status.p, 0, status.bytes(), s));
+    hipLaunchKernelGGL(k_scan, dim3(static_cast<unsigned>(ntiles)), dim3(kScanBlock), 0, s, in, out, n, ntiles,
+                       status.p, total.p);
     PAIR_LAUNCH_CHECK();
-    if (ntiles > 1) {
-        exclusive_scan(sums.p, offs.p, ntiles, s);
-        hipLaunchKernelGGL(k_add_tile_offsets, dim3(grid_for(n, 256)), dim3(256), 0, s, out, n,
-                           offs.p);
-        PAIR_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(k_set_total, dim3(1), dim3(1), 0, s, out, n, in + (n - 1), out + (n - 1));
-    PAIR_LAUNCH_CHECK();
-    int64_t total = 0;
-    read_back(&total, out + n, 1, s);
-    return total;
+    PAIR_HIP(hipStreamSynchronize(s));
+    return *total.p;
 }
 
 // ---------------------------------------------------------------- segments
 namespace {
-__global__ void k_fill_seg(uint16_t* seg, int64_t begin, int64_t count, uint16_t id) {
-    int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g < count) seg[begin + g] = id;
+// Member of every row, all members in one launch (blockIdx.y: the member).
+__global__ void __launch_bounds__(256)
+k_fill_seg(uint16_t* __restrict__ seg, const int64_t* __restrict__ off, const int64_t* __restrict__ cnt) {
+    const int b = blockIdx.y;
+    const int64_t o = off[b], n = cnt[b];
+    if (o < 0) return;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
+         i += static_cast<int64_t>(gridDim.x) * 256)
+        seg[o + i] = static_cast<uint16_t>(b);
 }
 }  // namespace
 
-void fill_segments(uint16_t* seg, int64_t n, const std::vector<int64_t>& off,
-                   const std::vector<int64_t>& cnt, hipStream_t s) {
-    (void)n;
-    for (size_t b = 0; b < off.size(); ++b) {
-        if (off[b] < 0 || cnt[b] == 0) continue;
-        hipLaunchKernelGGL(k_fill_seg, dim3(grid_for(cnt[b], 256)), dim3(256), 0, s, seg, off[b],
-                           cnt[b], static_cast<uint16_t>(b));
-        PAIR_LAUNCH_CHECK();
-    }
+void fill_segments(uint16_t* seg, int members, int64_t most, const int64_t* off_d, const int64_t* cnt_d,
+                   hipStream_t s) {
+    const unsigned gx = static_cast<unsigned>(std::min<int64_t>((most + 2047) / 2048, 4096));
+    hipLaunchKernelGGL(k_fill_seg, dim3(std::max(1u, gx), static_cast<unsigned>(members)), dim3(256), 0, s, seg,
+                       off_d, cnt_d);
+    PAIR_LAUNCH_CHECK();
 }
 
 int choose_lpr(double avg) {
