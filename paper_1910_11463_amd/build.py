@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 OUT = os.path.join(HERE, "libpair.so")
 BUILD = os.path.join(ROOT, "_build")
 
-SOURCES = ["primitives.hip", "amg_setup.hip", "amg_solve.hip", "assemble.hip",
+SOURCES = ["primitives.hip", "amg_setup.hip", "amg_solve.hip", "amg_tail.hip", "assemble.hip",
            "transport.cpp", "quadrature.cpp", "api.cpp", "profile.cpp", "tet_schedule.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

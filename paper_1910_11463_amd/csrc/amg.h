@@ -164,6 +164,7 @@ struct Level {
     DBuf<uint8_t> relax;           // device copy
     // dense coarse solves of members whose coarsest level is this one
     std::vector<int> coarse_members;
+    int coarse_launch = 0;         // of them, solved by k_coarse_solve (the others in the tail)
     DBuf<int> coarse_member_d;     // member ids
     DBuf<int64_t> coarse_off_d;    // first row of each coarse member
     DBuf<int64_t> coarse_n_d;      // rows of each coarse member
@@ -176,15 +177,25 @@ struct Level {
     int lpr_r = 8;                 // lanes per row for kernels on R
 };
 
-// The solve's per-member scratch as plain device pointers: either the
-// hierarchy's own SolveBufs (and finest-level member offsets / counts), or a
-// caller-provided region carved by Hierarchy::carve_solve_scratch.
+// The small levels of a V-cycle as the tail kernel reads them (amg_tail.hip).
+struct TailLevel;
+constexpr int kTailLevels = 32;                // options.max_levels <= 32
+// Rows of a member on its first tail level, at most: where one workgroup per member
+// stops being faster than a launch per half-sweep that has the whole chip.  Limits of
+// 400 / 1024 / 2048: an 8^3 S2 sweep (1357 rows, 8 members) 925 / 918 / 912 us
+// (1088 without), a 24^3 tet S4 solve 125.7 / 125.7 / 124.4 ms (125.7 without).
+constexpr int64_t kTailRows = 2048;
+constexpr size_t kTailLds = 150 * 1024;        // of the CU's 160 KB
+
 // A member's state after a convergence test, in pinned host memory.
 struct MemberResult {
     double relres, relres0;
     int iters, active;
 };
 
+// The solve's per-member scratch as plain device pointers: either the
+// hierarchy's own SolveBufs (and finest-level member offsets / counts), or a
+// caller-provided region carved by Hierarchy::carve_solve_scratch.
 struct SolveView {
     double* partial = nullptr;     // [chunks][members] partial sums of the norms
     double* bnorm2 = nullptr;      // per member
@@ -270,6 +281,8 @@ private:
     void filter_restriction(Level& L, const int32_t* c2f, int64_t nc);
     void residual_norms();
     void launch_cycle_and_test(bool x_is_zero, int it_offset);
+    void build_tail();
+    void launch_tail();
 
     AmgParams prm_;
     hipStream_t s_;
@@ -286,6 +299,16 @@ private:
     // member 0's rows and entries per level
     std::vector<int64_t> level_n0_, level_nnz0_;
     DBuf<int64_t> moff_d_, mcnt_d_;   // finest-level member offsets / counts
+    // the tail: packed levels of every member in it; levels with members that the
+    // level kernels still work on
+    bool tail_on_ = false;
+    size_t tail_lds_ = 0;
+    DBuf<uint16_t> tail_perm_, tail_col_;
+    DBuf<int2> tail_slice_, tail_mem_;
+    DBuf<double> tail_val_, tail_dinv_;
+    DBuf<int16_t> tail_p_;
+    DBuf<TailLevel> tail_lev_;
+    std::vector<uint8_t> level_on_;
     std::shared_ptr<FineEll> ell_;
     bool finest_identity_ = false;
     // captured cycles: graph_ any cycle, graph0_ the first cycle from x = 0

@@ -3379,6 +3379,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
     if (prm_.coarse_fp32) make_fp32_copies();
     note_level_sizes();
     if (prm_.tune) tune_lanes();
+    build_tail();
 }
 
 // Member 0's rows and entries on every level, read back in one launch (its

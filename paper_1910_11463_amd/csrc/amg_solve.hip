@@ -1622,10 +1622,10 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
     // down
     for (int l = 0; l < nl; ++l) {
         Level& L = levels_[l];
-        const bool has_relax = l + 1 < nl && L.R.n > 0;
-        if (!L.coarse_members.empty()) {
-            hipLaunchKernelGGL(k_coarse_solve, dim3(static_cast<unsigned>(L.coarse_members.size())),
-                               dim3(kBlock), 0, s_, static_cast<int>(L.coarse_members.size()),
+        const bool has_relax = l + 1 < nl && L.R.n > 0 && level_on_[l];
+        if (L.coarse_launch > 0) {
+            hipLaunchKernelGGL(k_coarse_solve, dim3(static_cast<unsigned>(L.coarse_launch)),
+                               dim3(kBlock), 0, s_, L.coarse_launch,
                                L.coarse_member_d.p, L.coarse_off_d.p, L.coarse_n_d.p,
                                L.coarse_inv_off_d.p, L.coarse_inv.p, act, L.b.p, L.x.p);
             PAIR_LAUNCH_CHECK();
@@ -1676,7 +1676,7 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
         PAIR_LAUNCH_CHECK();
         Level& C = levels_[l + 1];
         // with the next level's first half-sweep, where members relax there
-        const bool next_relaxes = l + 2 < nl && C.R.n > 0;
+        const bool next_relaxes = l + 2 < nl && C.R.n > 0 && level_on_[l + 1];
         const std::string& npre = prm_.relax_pre_coarse;
         const int8_t first = npre.empty() ? 0 : npre[0] == 'F' ? -1 : 1;
         double* xc = !next_relaxes ? nullptr : npre.empty() ? C.x.p : C.t.p;
@@ -1696,10 +1696,11 @@ void Hierarchy::vcycle_launches(bool x_is_zero) {
         });
         PAIR_LAUNCH_CHECK();
     }
+    if (tail_on_) launch_tail();
     // up
     for (int l = nl - 2; l >= 0; --l) {
         Level& L = levels_[l];
-        if (L.R.n == 0) continue;
+        if (L.R.n == 0 || !level_on_[l]) continue;
         Level& C = levels_[l + 1];
         const int64_t n = L.A.n;
         // into the buffer from which the schedule ends in x

@@ -1,0 +1,84 @@
+"""The small levels of a V-cycle in one launch (at most 2048 rows of a member on
+the first of them): sizes around that limit, members of different depth in one
+batch, every schedule, and rows of many lengths."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(n, fill, seed):
+    """A diagonally dominant random matrix (CSR) with rows of very different
+    lengths; 1 / (1 - 0.8) bounds its inverse in the maximum norm."""
+    rng = np.random.default_rng(seed)
+    rows, cols, vals = [], [], []
+    for i in range(n):
+        k = int(min(n - 1, rng.integers(0, fill) * rng.integers(0, 3)))
+        c = np.unique(rng.integers(0, n, size=k))
+        c = c[c != i]
+        v = rng.uniform(0.1, 1.0, len(c))
+        if len(c):
+            v *= -0.8 / v.sum()
+        c = np.append(c, i)
+        v = np.append(v, 1.0)
+        o = np.argsort(c)
+        rows.append(np.full(len(c), i))
+        cols.append(c[o])
+        vals.append(v[o])
+    rowptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    return rowptr, np.concatenate(cols).astype(np.int32), np.concatenate(vals)
+
+
+def _batch(mats):
+    rp, ci, va, seg = [np.zeros(1, np.int64)], [], [], [0]
+    for rowptr, col, val in mats:
+        rp.append(rowptr[1:] + rp[-1][-1])
+        ci.append(col + seg[-1])
+        va.append(val)
+        seg.append(seg[-1] + len(rowptr) - 1)
+    return np.concatenate(rp), np.concatenate(ci).astype(np.int32), np.concatenate(va), seg
+
+
+def _dense(m):
+    rowptr, col, val = m
+    n = len(rowptr) - 1
+    A = np.zeros((n, n))
+    A[np.repeat(np.arange(n), np.diff(rowptr)), col] = val
+    return A
+
+
+# finest levels from one row up to past the limit: the tail starts on the first
+# coarse level of the small ones, further down or nowhere for the others
+SIZES = [1, 63, 64, 65, 130, 700, 2047, 2300]
+
+
+@pytest.mark.parametrize("pre,post", [("FC", "FC"), ("F", ""), ("FFC", "C"), ("", "F")])
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_members_of_every_size(pre, post, fp32):
+    """Every member alone and in one batch: the same iterates bit for bit, and the
+    dense solution (tol_inner 1e-11 times 5, the bound of the inverse, times the
+    ratio of the norms, below sqrt(2300) = 48)."""
+    need_gpu()
+    from paper_1910_11463_amd.solver import Amg
+    mats = [_matrix(n, 14, n) for n in SIZES]
+    opts = dict(tol_inner=1e-11, max_inner=400, relax_pre="FC", relax_post="FC", relax_pre_coarse=pre,
+                relax_post_coarse=post, coarse_fp32=fp32)
+    rng = np.random.default_rng(5)
+    b = [rng.uniform(-1.0, 1.0, n) for n in SIZES]
+    rowptr, col, val, seg = _batch(mats)
+    a = Amg(**opts)
+    a.setup(rowptr, col, val, seg)
+    x, it, rel, rc = a.solve(np.concatenate(b))
+    assert rc == 0, rel
+    for s, m in enumerate(mats):
+        one = Amg(**opts)
+        one.setup(*m)
+        y, it1, _, rc1 = one.solve(b[s])
+        assert rc1 == 0 and it1[0] == it[s]
+        assert np.array_equal(x[seg[s]:seg[s + 1]], y), SIZES[s]
+        ref = np.linalg.solve(_dense(m), b[s])
+        assert np.abs(y - ref).max() <= 1e-11 * 5 * 48 * max(1.0, np.abs(b[s]).max()) + 1e-13
+        one.close()
+    a.close()
