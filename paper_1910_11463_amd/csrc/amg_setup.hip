@@ -44,7 +44,10 @@ constexpr uint64_t KEY_NONE = ~0ull;
 // flags of every entry and lambda (number of rows strongly depending on a column).
 // entries per lane held in registers for short rows: 8 (32 per row) covers the
 // coarse levels' rows, which with 4 (16 per row) were read twice (64^3 S8
-// benchmark, first coarse level: 1.73 -> 1.13 ms per launch)
+// benchmark, first coarse level: 1.73 -> 1.13 ms per launch).  HBM and the latency
+// of a row bound it: a lane's loads go out together, half as many where the wave's
+// rows have at most half (48^3, 16 directions, finest level: 1099 -> 981 us against
+// loads one by one).
 constexpr int kStrengthPerLane = 8;
 
 template <int G>
@@ -59,21 +62,24 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
     if (row >= n) return;
     const int64_t rs = rowptr[row], re = rowptr[row + 1];
     double d = 0.0, m = 0.0;
-    if (re - rs <= kStrengthPerLane * G) {
-        // short row: one pass, the entries kept in registers
-        int32_t cr[kStrengthPerLane];
-        double vr[kStrengthPerLane];
+    const int len = static_cast<int>(re - rs);
+    // U entries per lane: loaded together (places past the row's end read its last
+    // entry), kept in registers
+    auto in_registers = [&](auto count) {
+        constexpr int U = decltype(count)::value;
+        int32_t cr[U];
+        double vr[U];
 #pragma unroll
-        for (int u = 0; u < kStrengthPerLane; ++u) {
-            const int64_t e = rs + u * G + sub;
-            cr[u] = -1;
-            vr[u] = 0.0;
-            if (e < re) {
-                cr[u] = col[e];
-                vr[u] = val[e];
-                if (cr[u] == row) d = vr[u];
-                else m = fmax(m, fabs(vr[u]));
-            }
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = rs + min(u * G + sub, len - 1);
+            cr[u] = col[e];
+            vr[u] = val[e];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u * G + sub >= len) cr[u] = -1;
+            else if (cr[u] == row) d = vr[u];
+            else m = fmax(m, fabs(vr[u]));
         }
         m = group_max<G>(m);
         d = group_sum<G>(d);
@@ -81,16 +87,15 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
         const bool on = part[seg[row]] != 0 && m > 0.0;
         int ns = 0;
 #pragma unroll
-        for (int u = 0; u < kStrengthPerLane; ++u) {
-            const int64_t e = rs + u * G + sub;
-            if (e >= re) continue;
+        for (int u = 0; u < U; ++u) {
+            if (cr[u] < 0) continue;
             uint8_t f = 0;
             if (on && cr[u] != row) {
                 const double a = fabs(vr[u]);
                 if (a >= theta * m) f |= 1;
                 if (a >= eps_r * m) f |= 2;
             }
-            sflag[e] = f;
+            sflag[rs + u * G + sub] = f;
             if (f & 1) {
                 atomicAdd(&lam[cr[u]], 1);
                 ++ns;
@@ -98,6 +103,10 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
         }
         ns = group_sum_int<G>(ns);
         if (sub == 0) scnt[row] = ns;
+    };
+    if (len <= kStrengthPerLane * G && len > 0) {
+        if (__all(len <= kStrengthPerLane / 2 * G)) in_registers(std::integral_constant<int, kStrengthPerLane / 2>());
+        else in_registers(std::integral_constant<int, kStrengthPerLane>());
         return;
     }
     for (int64_t e = rs + sub; e < re; e += G) {
@@ -130,7 +139,9 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
 
 // The strong (theta) entries of each row, in column order, as their own CSR
 // (scol / sval at srp[i] ..): the PMIS rounds and the interpolation read only
-// these.  G lanes per row.
+// these.  G lanes per row, kFillLoads entries of each lane loaded together (48^3, 16
+// directions, finest level: 911 -> 776 us against flag first, then column and value).
+constexpr int kFillLoads = 2;
 template <int G>
 __global__ void __launch_bounds__(256)
 k_strong_fill(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
@@ -142,146 +153,188 @@ k_strong_fill(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __re
     if (row >= n) return;
     const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << (lane & ~(G - 1)));
     const int64_t rs = rowptr[row], re = rowptr[row + 1];
+    const int len = static_cast<int>(re - rs);
     int64_t pos = srp[row];
-    for (int64_t e0 = rs; e0 < re; e0 += G) {
-        const int64_t e = e0 + sub;
-        const bool st = e < re && (sflag[e] & 1);
-        const uint64_t m = __ballot(st) & gmask;
-        if (st) {
-            const int64_t q = pos + __popcll(m & ((1ull << lane) - 1ull));
-            scol[q] = col[e];
-            sval[q] = val[e];
+    for (int e0 = 0; e0 < len; e0 += kFillLoads * G) {
+        uint8_t f[kFillLoads];
+        int32_t c[kFillLoads];
+        double v[kFillLoads];
+#pragma unroll
+        for (int u = 0; u < kFillLoads; ++u) {
+            const int64_t e = rs + min(e0 + u * G + sub, len - 1);
+            f[u] = sflag[e];
+            c[u] = col[e];
+            v[u] = val[e];
         }
-        pos += __popcll(m);
+#pragma unroll
+        for (int u = 0; u < kFillLoads; ++u) {
+            const bool st = e0 + u * G + sub < len && (f[u] & 1);
+            const uint64_t m = __ballot(st) & gmask;
+            if (st) {
+                const int64_t q = pos + __popcll(m & ((1ull << lane) - 1ull));
+                scol[q] = c[u];
+                sval[q] = v[u];
+            }
+            pos += __popcll(m);
+        }
     }
 }
 
 // ------------------------------------------------------------- PMIS
-__device__ __forceinline__ bool key_less(int li, uint64_t ri, int64_t ii, int lj, uint64_t rj,
-                                         int64_t ij) {
-    if (li != lj) return li < lj;
-    if (ri != rj) return ri < rj;
-    return ii < ij;
-}
-
-
-
-
-
-
 // List-driven rounds: the undecided rows of a round are listed (in any order;
-// every decision depends only on the states, so the split is reproducible).
-// Kernels read the list length from device memory, so several rounds can be
-// queued without host synchronisation.
-// kRowsPT consecutive rows per thread, one list reservation per block: the
-// lists keep ascending row order within a block, which the kernels reading
-// them rely on for locality.
+// every decision depends only on the keys and marks, so the split is
+// reproducible).  Kernels read the list length from device memory, so several
+// rounds can be queued without host synchronisation.
+//
+// A point's key orders (lambda, random value, local index): lambda in the top 11
+// bits (at most 2047), its 53-bit random value below; 0 once it is decided.  Equal
+// keys, and two of lambda >= 2047, are compared in full.  A point's mark is
+// kMarkC, kMarkF, or, undecided, the parity mark (1 or 2) of the last round in
+// which a strong neighbour beat it: every point that stays undecided was beaten in
+// the round before, so a mark of the current parity was set in the current round.
+// What bounds the rounds is the gathers at the columns: one of 8 bytes (key) per
+// entry in the compare pass and one byte (mark) in the mark pass, four entries per
+// lane in flight.  48^3, 16 directions, finest level, 15 rounds, compare / mark:
+// state, lambda and a hash per entry, states and flags apart 992 / 864 us; so
+// 687 / 856; with 2 or 3 entries in flight 750 / 919 and 720 / 873.
+// kRowsPT rows per thread, one list reservation per block: the lists keep
+// ascending row order within a block, which the kernels reading them rely on for
+// locality.
 constexpr int kRowsPT = 8;
+constexpr uint8_t kMarkF = 254, kMarkC = 255;
+constexpr int kPmisLoads = 4;       // entries per lane in flight
 
 __global__ void __launch_bounds__(256)
-k_pmis_init_list(int64_t n, const uint16_t* __restrict__ seg,
-                                 const uint8_t* __restrict__ part, const int* __restrict__ lam,
-                                 int8_t* __restrict__ state, int32_t* __restrict__ list,
-                                 int* __restrict__ cnt) {
-    const int64_t base = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * kRowsPT;
+k_pmis_init_list(int64_t n, const uint16_t* __restrict__ seg, const int64_t* __restrict__ off,
+                 const uint8_t* __restrict__ part, const int* __restrict__ lam, int level, uint64_t seed,
+                 int8_t* __restrict__ state, uint64_t* __restrict__ key, uint8_t* __restrict__ mark,
+                 int32_t* __restrict__ list, int* __restrict__ cnt) {
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * 256 * kRowsPT + threadIdx.x;
     unsigned und = 0;
 #pragma unroll
     for (int r = 0; r < kRowsPT; ++r) {
-        const int64_t i = base + r;
+        const int64_t i = base + r * 256;
         if (i < n) {
-            if (!part[seg[i]]) state[i] = ST_NP;
-            else if (lam[i] == 0) state[i] = ST_F;
-            else { state[i] = ST_U; und |= 1u << r; }
+            const int sg = seg[i], li = lam[i];
+            const bool np = !part[sg], u = !np && li != 0;
+            state[i] = np ? ST_NP : u ? ST_U : ST_F;
+            mark[i] = u ? 0 : kMarkF;
+            key[i] = u ? static_cast<uint64_t>(min(li, 2047)) << 53 | pmis_rand(seed, level, i - off[sg]) : 0;
+            if (u) und |= 1u << r;
         }
     }
-    int slot = block_reserve<256>(__popc(und), cnt);
+    int slot[kRowsPT];
+    block_reserve_rows<256, kRowsPT>(und, cnt, slot);
 #pragma unroll
     for (int r = 0; r < kRowsPT; ++r)
-        if ((und >> r) & 1u) list[slot++] = static_cast<int32_t>(base + r);
+        if ((und >> r) & 1u) list[slot[r]] = static_cast<int32_t>(base + r * 256);
 }
 
 // G lanes per undecided row, striding over its entries.  For every strong
-// pair of undecided points the one with the smaller key (lambda, random value,
-// local index) is marked as not a local maximum.
+// pair of undecided points the one with the smaller key is marked as not a local
+// maximum.
 template <int G>
-__global__ void k_pmis_compare_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
-                                    const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-                                    const int8_t* __restrict__ state,
-                                    const int* __restrict__ lam, const uint16_t* __restrict__ seg,
-                                    const int64_t* __restrict__ off, int level, uint64_t seed,
-                                    uint8_t* __restrict__ notmax, int* __restrict__ next_cnt) {
+__global__ void __launch_bounds__(256)
+k_pmis_compare_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
+                    const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                    const uint64_t* __restrict__ key, const int* __restrict__ lam, uint8_t beaten,
+                    uint8_t* __restrict__ mark, int* __restrict__ next_cnt) {
     const int c = *cnt;
     if (blockIdx.x == 0 && threadIdx.x == 0) *next_cnt = 0;   // the next list is built by the mark pass
     const int sub = threadIdx.x & (G - 1);
     const int stride = gridDim.x * (blockDim.x / G);
     for (int k = (blockIdx.x * blockDim.x + threadIdx.x) / G; k < c; k += stride) {
-        const int64_t i = list[k];
-        const int64_t base = off[seg[i]];
-        const int64_t li = i - base;
-        const uint64_t ri = pmis_rand(seed, level, li);
-        const int lami = lam[i];
-        const int64_t re = rowptr[i + 1];
-        for (int64_t e = rowptr[i] + sub; e < re; e += G) {
-            const int64_t j = col[e];
-            if (state[j] != ST_U) continue;
-            const int64_t lj = j - base;
-            if (key_less(lami, ri, li, lam[j], pmis_rand(seed, level, lj), lj)) notmax[i] = 1;
-            else notmax[j] = 1;
+        const int32_t i = list[k];
+        const uint64_t ki = key[i];
+        const int64_t rs = rowptr[i];
+        const int len = static_cast<int>(rowptr[i + 1] - rs);
+        bool less = false;
+        for (int e = sub; e < len; e += kPmisLoads * G) {
+            int32_t j[kPmisLoads];
+            uint64_t kj[kPmisLoads];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) kj[u] = key[j[u]];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) {
+                if (kj[u] == 0 || e + u * G >= len) continue;
+                bool l = ki < kj[u];
+                if (ki == kj[u] || ((ki & kj[u]) >> 53) == 2047) {
+                    const int a = lam[i], b = lam[j[u]];
+                    const uint64_t m = (1ull << 53) - 1;
+                    l = a != b ? a < b : (ki & m) != (kj[u] & m) ? (ki & m) < (kj[u] & m) : i < j[u];
+                }
+                if (l) less = true;
+                else mark[j[u]] = beaten;
+            }
         }
+        if (less) mark[i] = beaten;
     }
 }
 
 // Selection and marking of one round in one pass.  An undecided row that no
-// strong neighbour beat (notmax == 0) becomes C.  Otherwise it becomes F if a
-// strong neighbour is C, either decided earlier or selected in this round
-// (undecided with notmax == 0: its own thread may be writing C at the same
-// time, and either value it reads means C); rows left undecided form the next
-// round's list.  Each row also clears its flag in the other notmax buffer,
-// which the next round's compare pass fills.  G lanes per row, NT-thread
-// blocks; the loop runs the same number of times on every thread of a block,
-// so all reach block_append.
-template <int G, int NT>
+// strong neighbour beat becomes C.  Otherwise it becomes F if a strong neighbour
+// is C, either decided earlier or selected in this round (undecided and not
+// beaten: its own thread may be writing C at the same time, and either value it
+// reads means C; a beaten one's may be writing F, and either means not C); rows
+// left undecided form the next round's list.  G lanes per row, NT-thread blocks, R
+// rows per thread and list reservation; the loop runs the same number of times on
+// every thread of a block, so all reach block_reserve_rows.
+template <int G, int NT, int R>
 __global__ void __launch_bounds__(NT)
 k_pmis_mark_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
-                 const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-                 int8_t* __restrict__ state,
-                 const uint8_t* __restrict__ notmax, uint8_t* __restrict__ notmax_other,
+                 const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col, uint8_t beaten,
+                 int8_t* __restrict__ state, uint64_t* __restrict__ key, uint8_t* mark,
                  int32_t* __restrict__ next, int* __restrict__ next_cnt) {
-    constexpr int RPB = NT / G;   // rows per block and iteration
+    constexpr int RPB = NT / G;   // rows per block and step
     const int c = *cnt;
     const int lane = threadIdx.x & 63;
     const int sub = lane & (G - 1);
     const int gbase = lane & ~(G - 1);
-    const int stride = gridDim.x * RPB;
-    for (int kb = blockIdx.x * RPB; kb < c; kb += stride) {
-        const int k = kb + static_cast<int>(threadIdx.x) / G;
-        int32_t i = -1;
-        bool live = false, sel = false;
-        if (k < c) {
-            i = list[k];
-            live = true;   // every row of the list is undecided at the start of the round
-            sel = notmax[i] == 0;
+    const int stride = gridDim.x * RPB * R;
+    for (int kb = blockIdx.x * RPB * R; kb < c; kb += stride) {
+        int32_t row[R];
+        unsigned keep = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int k = kb + r * RPB + static_cast<int>(threadIdx.x) / G;
+            row[r] = k < c ? list[k] : -1;     // undecided at the start of the round
         }
-        bool f = false;
-        if (live && !sel) {
-            const int64_t re = rowptr[i + 1];
-            for (int64_t e = rowptr[i] + sub; e < re; e += G) {
-                const int32_t j = col[e];
-                const int8_t sj = state[j];
-                if (sj == ST_C || (sj == ST_U && notmax[j] == 0)) { f = true; break; }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t i = row[r];
+            bool sel = false, f = false;
+            if (i >= 0) {
+                const int64_t rs = rowptr[i];
+                const int len = static_cast<int>(rowptr[i + 1] - rs);
+                sel = mark[i] != beaten;
+                for (int e = sub; e < len && !sel && !f; e += kPmisLoads * G) {
+                    int32_t j[kPmisLoads];
+                    uint8_t m[kPmisLoads];
+#pragma unroll
+                    for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
+#pragma unroll
+                    for (int u = 0; u < kPmisLoads; ++u) m[u] = mark[j[u]];
+#pragma unroll
+                    for (int u = 0; u < kPmisLoads; ++u) f |= m[u] != beaten && m[u] != kMarkF;
+                }
             }
+            const uint64_t fm = __ballot(f);
+            const bool anyf = ((fm >> gbase) & ((G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull))) != 0;
+            const bool lead = i >= 0 && sub == 0;
+            if (lead && (sel || anyf)) {
+                mark[i] = sel ? kMarkC : kMarkF;
+                key[i] = 0;
+                state[i] = sel ? ST_C : ST_F;
+            }
+            if (lead && !sel && !anyf) keep |= 1u << r;
         }
-        const uint64_t fm = __ballot(f);
-        const bool anyf = ((fm >> gbase) & ((G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull))) != 0;
-        const bool lead = live && sub == 0;
-        if (lead) {
-            notmax_other[i] = 0;
-            if (sel) state[i] = ST_C;
-            else if (anyf) state[i] = ST_F;
-        }
-        const bool keep = lead && !sel && !anyf;
-        const int slot = block_append<NT>(keep, next_cnt);
-        if (keep) next[slot] = i;
+        int slot[R];
+        block_reserve_rows<NT, R>(keep, next_cnt, slot);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if ((keep >> r) & 1u) next[slot[r]] = row[r];
     }
 }
 
@@ -298,11 +351,11 @@ template <int NC>
 __global__ void __launch_bounds__(256)
 k_classify(int64_t n, int mode, const int64_t* __restrict__ a, const int64_t* __restrict__ ub,
            RowClasses rc, int* __restrict__ cnt, const uint8_t* __restrict__ mask) {
-    const int64_t base = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * kRowsPT;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * 256 * kRowsPT + threadIdx.x;
     int8_t cls[kRowsPT];
 #pragma unroll
     for (int r = 0; r < kRowsPT; ++r) {
-        const int64_t i = base + r;
+        const int64_t i = base + r * 256;
         cls[r] = -1;
         if (i < n && (!mask || mask[i])) {
             const int64_t v = mode == 2 ? ub[i] : (a[i + 1] - a[i] - (mode == 1 ? 1 : 0));
@@ -314,13 +367,14 @@ k_classify(int64_t n, int mode, const int64_t* __restrict__ a, const int64_t* __
     }
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
-        int c = 0;
+        unsigned in = 0;
 #pragma unroll
-        for (int r = 0; r < kRowsPT; ++r) c += cls[r] == k ? 1 : 0;
-        int slot = block_reserve<256>(c, &cnt[k]);
+        for (int r = 0; r < kRowsPT; ++r) in |= cls[r] == k ? 1u << r : 0u;
+        int slot[kRowsPT];
+        block_reserve_rows<256, kRowsPT>(in, &cnt[k], slot);
 #pragma unroll
         for (int r = 0; r < kRowsPT; ++r)
-            if (cls[r] == k) rc.list[k][slot++] = static_cast<int32_t>(base + r);
+            if (cls[r] == k) rc.list[k][slot[r]] = static_cast<int32_t>(base + r * 256);
     }
 }
 
@@ -413,11 +467,10 @@ k_cf_counts(int64_t n, const int64_t* __restrict__ rowptr, const int8_t* __restr
     }
 }
 
-// One-point interpolation: the strongest strong C neighbour (largest |a_ij|,
-// then smallest column), one thread per row.
 // One-point interpolation, G lanes per row: an F row takes the strongest
 // strong C neighbour, the smallest column among equal magnitudes (the lanes'
-// candidates are combined by (magnitude, column)).
+// candidates are combined by (magnitude, column)); two entries of a lane loaded
+// together (48^3, 16 directions, finest level: 561 -> 460 us against one).
 template <int G>
 __global__ void __launch_bounds__(256)
 k_interp(int64_t n, const int64_t* __restrict__ srp, const int32_t* __restrict__ scol,
@@ -437,13 +490,23 @@ k_interp(int64_t n, const int64_t* __restrict__ srp, const int32_t* __restrict__
     }
     double best = -1.0;
     int32_t bj = 0x7fffffff;
-    const int64_t se = srp[i + 1];
-    for (int64_t e = srp[i] + sub; e < se; e += G) {
-        const int32_t j = scol[e];
-        if (cf[j] > 0) {
-            const double a = fabs(sval[e]);
-            if (a > best || (a == best && j < bj)) { best = a; bj = j; }
+    const int64_t ss = srp[i];
+    const int len = static_cast<int>(srp[i + 1] - ss);
+    for (int e = sub; e < len; e += 2 * G) {       // two entries loaded together
+        int32_t j[2];
+        double a[2];
+        int8_t cj[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t q = ss + min(e + u * G, len - 1);
+            j[u] = scol[q];
+            a[u] = fabs(sval[q]);
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) cj[u] = cf[j[u]];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (cj[u] > 0 && (a[u] > best || (a[u] == best && j[u] < bj))) { best = a[u]; bj = j[u]; }
     }
 #pragma unroll
     for (int d = G / 2; d >= 1; d >>= 1) {
@@ -2831,15 +2894,15 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
 
         // PMIS: list-driven rounds, host check every few rounds
         DBuf<int8_t> state(n);
-        DBuf<uint8_t> notmax(2 * n);   // one flag buffer per round parity
+        DBuf<uint64_t> pkey(n);
+        DBuf<uint8_t> mark(n);
         DBuf<int32_t> plist[2];
         plist[0].alloc(n);
         plist[1].alloc(n);
         DBuf<int> pcnt(2);
         PAIR_HIP(hipMemsetAsync(pcnt.p, 0, 2 * sizeof(int), s_));
-        PAIR_HIP(hipMemsetAsync(notmax.p, 0, 2 * n, s_));
         hipLaunchKernelGGL(k_pmis_init_list, dim3(grid_for(n, 256 * kRowsPT)), dim3(256), 0, s_, n, L.seg.p,
-                           d_part.p, lam.p, state.p, plist[0].p, pcnt.p);
+                           d_off.p, d_part.p, lam.p, l, prm_.seed, state.p, pkey.p, mark.p, plist[0].p, pcnt.p);
         PAIR_LAUNCH_CHECK();
         {
             constexpr int kPmisG = 2;   // lanes per row (rows of ~13 entries: 2 beat 1, 4, 8, 16)
@@ -2850,16 +2913,14 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             for (int round = 0;; ++round) {
                 PAIR_CHECK(round < 100000, "PMIS did not terminate");
                 const int nxt = cur ^ 1;
-                uint8_t* nm_cur = notmax.p + (round & 1) * n;
-                uint8_t* nm_other = notmax.p + ((round & 1) ^ 1) * n;
+                const uint8_t beaten = static_cast<uint8_t>(1 + (round & 1));
                 const unsigned pg = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 256), 8192));
                 hipLaunchKernelGGL(k_pmis_compare_list<kPmisG>, dim3(pg), dim3(256), 0, s_, plist[cur].p,
-                                   pcnt.p + cur, srp.p, scol.p, state.p, lam.p,
-                                   L.seg.p, d_off.p, l, prm_.seed, nm_cur, pcnt.p + nxt);
-                const unsigned pgm = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 1024), 2048));
-                hipLaunchKernelGGL((k_pmis_mark_list<kPmisG, 1024>), dim3(pgm), dim3(1024), 0, s_, plist[cur].p,
-                                   pcnt.p + cur, srp.p, scol.p, state.p, nm_cur,
-                                   nm_other, plist[nxt].p, pcnt.p + nxt);
+                                   pcnt.p + cur, srp.p, scol.p, pkey.p, lam.p, beaten, mark.p, pcnt.p + nxt);
+                const unsigned pgm = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 1024), 8192));
+                hipLaunchKernelGGL((k_pmis_mark_list<kPmisG, 256, 4>), dim3(pgm), dim3(256), 0, s_, plist[cur].p,
+                                   pcnt.p + cur, srp.p, scol.p, beaten, state.p, pkey.p, mark.p, plist[nxt].p,
+                                   pcnt.p + nxt);
                 PAIR_LAUNCH_CHECK();
                 cur = nxt;
                 if (round % 3 == 2) {

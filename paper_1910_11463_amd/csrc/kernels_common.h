@@ -95,61 +95,43 @@ __device__ __forceinline__ int64_t tile_ticket(unsigned* counter, unsigned* shar
     return *shared;
 }
 
-// Append to a global list with one atomic per block: every thread of the
-// one-dimensional NT-thread block must call this.  Returns the slot of the
-// calling thread, or -1.  The order of entries across blocks is not fixed.
-template <int NT>
-__device__ __forceinline__ int block_append(bool pred, int* counter) {
-    __shared__ int s_cnt[NT / 64];
-    __shared__ int s_base;
+// Appends to a global list with one atomicAdd on `counter` per block: R rows per
+// thread that lie NT apart (so that the block's accesses to them are contiguous),
+// bit r of `bits` keeps row r * NT + threadIdx.x of the tile, slot[r] is its place,
+// in row order.  Every thread of the NT-thread block must call it.  The order of
+// entries across blocks is not fixed.
+template <int NT, int R>
+__device__ __forceinline__ void block_reserve_rows(unsigned bits, int* counter, int (&slot)[R]) {
+    constexpr int W = NT / 64;
+    static_assert(R * W <= 64, "one wave scans the counts");
+    __shared__ int s_c[R * W];
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint64_t m = __ballot(pred);
-    if (lane == 0) s_cnt[wid] = __popcll(m);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            const int t = s_cnt[w];
-            s_cnt[w] = tot;
-            tot += t;
-        }
-        s_base = tot > 0 ? atomicAdd(counter, tot) : 0;
-    }
-    __syncthreads();
-    const int slot = s_base + s_cnt[wid] + __popcll(m & ((1ull << lane) - 1ull));
-    __syncthreads();   // the next call may overwrite s_cnt / s_base
-    return pred ? slot : -1;
-}
-
-// Reserves c consecutive slots per thread in a global list (block-wide
-// exclusive scan of c, one atomicAdd on `counter` per block); returns the
-// thread's first slot.  Every thread of the NT-thread block must call it.
-template <int NT>
-__device__ __forceinline__ int block_reserve(int c, int* counter) {
-    __shared__ int s_w[NT / 64];
-    __shared__ int s_base;
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int x = c;
+    const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
+    for (int r = 0; r < R; ++r) {
+        const uint64_t m = __ballot((bits >> r) & 1u);
+        slot[r] = __popcll(m & below);
+        if (lane == 0) s_c[r * W + wid] = __popcll(m);
     }
-    if (lane == 63) s_w[wid] = x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            const int t = s_w[w];
-            s_w[w] = tot;
-            tot += t;
+    if (wid == 0) {
+        const int c = lane < R * W ? s_c[lane] : 0;
+        int x = c;
+#pragma unroll
+        for (int d = 1; d < R * W; d <<= 1) {
+            const int y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
         }
-        s_base = tot > 0 ? atomicAdd(counter, tot) : 0;
+        const int tot = __shfl(x, R * W - 1, 64);
+        int base = 0;
+        if (lane == 0 && tot > 0) base = atomicAdd(counter, tot);
+        base = __shfl(base, 0, 64);
+        if (lane < R * W) s_c[lane] = base + x - c;
     }
     __syncthreads();
-    const int slot = s_base + s_w[wid] + x - c;
-    __syncthreads();   // the next call may overwrite s_w / s_base
-    return slot;
+#pragma unroll
+    for (int r = 0; r < R; ++r) slot[r] += s_c[r * W + wid];
+    __syncthreads();   // the next call may overwrite s_c
 }
 
 // SplitMix64 (Steele, Lea & Flood 2014): add the golden-ratio increment, then
