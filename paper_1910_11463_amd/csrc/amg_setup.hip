@@ -44,11 +44,22 @@ constexpr uint64_t KEY_NONE = ~0ull;
 // flags of every entry and lambda (number of rows strongly depending on a column).
 // entries per lane held in registers for short rows: 8 (32 per row) covers the
 // coarse levels' rows, which with 4 (16 per row) were read twice (64^3 S8
-// benchmark, first coarse level: 1.73 -> 1.13 ms per launch).  HBM and the latency
-// of a row bound it: a lane's loads go out together, half as many where the wave's
-// rows have at most half (48^3, 16 directions, finest level: 1099 -> 981 us against
-// loads one by one).
+// benchmark, first coarse level: 1.73 -> 1.13 ms per launch).  HBM, the latency of a
+// row and lambda's atomics bound it: a lane's loads go out together, half as many
+// where the wave's rows have at most half (48^3, 16 directions, finest level: 1099
+// -> 981 us against loads one by one), and equal columns of rows side by side, which
+// an element's rows all have, count with one atomic (981 -> 676 us; without any
+// atomic 632 us; first coarse level 500 -> 428 us).
 constexpr int kStrengthPerLane = 8;
+
+// count (>= 0) of column c moves to the lower of lanes l and l ^ X where both hold
+// the same column; every lane of the wave takes part
+template <int X>
+__device__ __forceinline__ void add_equal(int32_t c, int& count) {
+    constexpr int kXor = 0x1F | (X << 10);
+    const int oc = __builtin_amdgcn_ds_swizzle(c, kXor), on = __builtin_amdgcn_ds_swizzle(count, kXor);
+    if (oc == c) count = (threadIdx.x & X) ? 0 : count + on;
+}
 
 template <int G>
 __global__ void __launch_bounds__(256)
@@ -59,32 +70,38 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
                  int64_t* __restrict__ scnt) {
     const int64_t row = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / G;
     const int sub = threadIdx.x % G;
-    if (row >= n) return;
-    const int64_t rs = rowptr[row], re = rowptr[row + 1];
+    const bool live = row < n;
+    const int64_t rs = live ? rowptr[row] : 0, re = live ? rowptr[row + 1] : 0;
     double d = 0.0, m = 0.0;
     const int len = static_cast<int>(re - rs);
     // U entries per lane: loaded together (places past the row's end read its last
-    // entry), kept in registers
-    auto in_registers = [&](auto count) {
+    // entry), kept in registers.  COMBINE (the whole wave is here): equal columns
+    // in one place of neighbouring rows count with one atomic.
+    auto in_registers = [&](auto count, auto combine) {
         constexpr int U = decltype(count)::value;
+        constexpr bool COMBINE = decltype(combine)::value;
         int32_t cr[U];
         double vr[U];
+        int strong[U];
+        if (len > 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = rs + min(u * G + sub, len - 1);
-            cr[u] = col[e];
-            vr[u] = val[e];
+            for (int u = 0; u < U; ++u) {
+                const int64_t e = rs + min(u * G + sub, len - 1);
+                cr[u] = col[e];
+                vr[u] = val[e];
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            strong[u] = 0;
             if (u * G + sub >= len) cr[u] = -1;
             else if (cr[u] == row) d = vr[u];
             else m = fmax(m, fabs(vr[u]));
         }
         m = group_max<G>(m);
         d = group_sum<G>(d);
-        if (sub == 0) dinv[row] = d != 0.0 ? 1.0 / d : 0.0;
-        const bool on = part[seg[row]] != 0 && m > 0.0;
+        if (live && sub == 0) dinv[row] = d != 0.0 ? 1.0 / d : 0.0;
+        const bool on = m > 0.0 && part[seg[row]] != 0;
         int ns = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -96,17 +113,32 @@ k_strength_fused(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* _
                 if (a >= eps_r * m) f |= 2;
             }
             sflag[rs + u * G + sub] = f;
-            if (f & 1) {
-                atomicAdd(&lam[cr[u]], 1);
-                ++ns;
+            strong[u] = f & 1;
+            ns += f & 1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (COMBINE) {
+                add_equal<4>(cr[u], strong[u]);
+                add_equal<8>(cr[u], strong[u]);
+                add_equal<16>(cr[u], strong[u]);
             }
+            if (strong[u] > 0) atomicAdd(&lam[cr[u]], strong[u]);
         }
         ns = group_sum_int<G>(ns);
-        if (sub == 0) scnt[row] = ns;
+        if (live && sub == 0) scnt[row] = ns;
     };
-    if (len <= kStrengthPerLane * G && len > 0) {
-        if (__all(len <= kStrengthPerLane / 2 * G)) in_registers(std::integral_constant<int, kStrengthPerLane / 2>());
-        else in_registers(std::integral_constant<int, kStrengthPerLane>());
+    constexpr int U = kStrengthPerLane;
+    if (__all(len <= U / 2 * G)) {
+        in_registers(std::integral_constant<int, U / 2>(), std::true_type());
+        return;
+    }
+    if (__all(len <= U * G)) {
+        in_registers(std::integral_constant<int, U>(), std::true_type());
+        return;
+    }
+    if (len <= U * G) {
+        in_registers(std::integral_constant<int, U>(), std::false_type());
         return;
     }
     for (int64_t e = rs + sub; e < re; e += G) {
