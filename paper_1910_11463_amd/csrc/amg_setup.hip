@@ -262,9 +262,79 @@ k_pmis_init_list(int64_t n, const uint16_t* __restrict__ seg, const int64_t* __r
         if ((und >> r) & 1u) list[slot[r]] = static_cast<int32_t>(base + r * 256);
 }
 
-// G lanes per undecided row, striding over its entries.  For every strong
-// pair of undecided points the one with the smaller key is marked as not a local
-// maximum.
+// One row of a compare pass (lane sub of its G lanes): of every strong pair of
+// undecided points the one with the smaller key is marked as not a local maximum.
+template <int G>
+__device__ __forceinline__ void pmis_compare_row(int32_t i, int sub, const int64_t* __restrict__ rowptr,
+                                                 const int32_t* __restrict__ col, const uint64_t* key,
+                                                 const int* __restrict__ lam, uint8_t beaten, uint8_t* mark) {
+    const uint64_t ki = key[i];
+    const int64_t rs = rowptr[i];
+    const int len = static_cast<int>(rowptr[i + 1] - rs);
+    bool less = false;
+    for (int e = sub; e < len; e += kPmisLoads * G) {
+        int32_t j[kPmisLoads];
+        uint64_t kj[kPmisLoads];
+#pragma unroll
+        for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
+#pragma unroll
+        for (int u = 0; u < kPmisLoads; ++u) kj[u] = key[j[u]];
+#pragma unroll
+        for (int u = 0; u < kPmisLoads; ++u) {
+            if (kj[u] == 0 || e + u * G >= len) continue;
+            bool l = ki < kj[u];
+            if (ki == kj[u] || ((ki & kj[u]) >> 53) == 2047) {
+                const int a = lam[i], b = lam[j[u]];
+                const uint64_t m = (1ull << 53) - 1;
+                l = a != b ? a < b : (ki & m) != (kj[u] & m) ? (ki & m) < (kj[u] & m) : i < j[u];
+            }
+            if (l) less = true;
+            else mark[j[u]] = beaten;
+        }
+    }
+    if (less) mark[i] = beaten;
+}
+
+// One row of a mark pass, decided if it can be; true (on lane sub == 0 of its G
+// lanes) if it stays undecided.  i < 0: no row; all lanes of the wave call it.  An
+// undecided row that no strong neighbour beat becomes C.  Otherwise it becomes F if
+// a strong neighbour is C, either decided earlier or selected in this round
+// (undecided and not beaten: its own thread may be writing C at the same time, and
+// either value it reads means C; a beaten one's may be writing F, and either means
+// not C).
+template <int G>
+__device__ __forceinline__ bool pmis_mark_row(int32_t i, int sub, const int64_t* __restrict__ rowptr,
+                                              const int32_t* __restrict__ col, uint8_t beaten,
+                                              int8_t* __restrict__ state, uint64_t* key, uint8_t* mark) {
+    const int gbase = static_cast<int>(threadIdx.x & 63) & ~(G - 1);
+    bool sel = false, f = false;
+    if (i >= 0) {
+        const int64_t rs = rowptr[i];
+        const int len = static_cast<int>(rowptr[i + 1] - rs);
+        sel = mark[i] != beaten;
+        for (int e = sub; e < len && !sel && !f; e += kPmisLoads * G) {
+            int32_t j[kPmisLoads];
+            uint8_t m[kPmisLoads];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) m[u] = mark[j[u]];
+#pragma unroll
+            for (int u = 0; u < kPmisLoads; ++u) f |= m[u] != beaten && m[u] != kMarkF;
+        }
+    }
+    const uint64_t fm = __ballot(f);
+    const bool anyf = ((fm >> gbase) & ((G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull))) != 0;
+    const bool lead = i >= 0 && sub == 0;
+    if (lead && (sel || anyf)) {
+        mark[i] = sel ? kMarkC : kMarkF;
+        key[i] = 0;
+        state[i] = sel ? ST_C : ST_F;
+    }
+    return lead && !sel && !anyf;
+}
+
+// The compare pass of a round, G lanes per row of the list.
 template <int G>
 __global__ void __launch_bounds__(256)
 k_pmis_compare_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
@@ -275,44 +345,13 @@ k_pmis_compare_list(const int32_t* __restrict__ list, const int* __restrict__ cn
     if (blockIdx.x == 0 && threadIdx.x == 0) *next_cnt = 0;   // the next list is built by the mark pass
     const int sub = threadIdx.x & (G - 1);
     const int stride = gridDim.x * (blockDim.x / G);
-    for (int k = (blockIdx.x * blockDim.x + threadIdx.x) / G; k < c; k += stride) {
-        const int32_t i = list[k];
-        const uint64_t ki = key[i];
-        const int64_t rs = rowptr[i];
-        const int len = static_cast<int>(rowptr[i + 1] - rs);
-        bool less = false;
-        for (int e = sub; e < len; e += kPmisLoads * G) {
-            int32_t j[kPmisLoads];
-            uint64_t kj[kPmisLoads];
-#pragma unroll
-            for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
-#pragma unroll
-            for (int u = 0; u < kPmisLoads; ++u) kj[u] = key[j[u]];
-#pragma unroll
-            for (int u = 0; u < kPmisLoads; ++u) {
-                if (kj[u] == 0 || e + u * G >= len) continue;
-                bool l = ki < kj[u];
-                if (ki == kj[u] || ((ki & kj[u]) >> 53) == 2047) {
-                    const int a = lam[i], b = lam[j[u]];
-                    const uint64_t m = (1ull << 53) - 1;
-                    l = a != b ? a < b : (ki & m) != (kj[u] & m) ? (ki & m) < (kj[u] & m) : i < j[u];
-                }
-                if (l) less = true;
-                else mark[j[u]] = beaten;
-            }
-        }
-        if (less) mark[i] = beaten;
-    }
+    for (int k = (blockIdx.x * blockDim.x + threadIdx.x) / G; k < c; k += stride)
+        pmis_compare_row<G>(list[k], sub, rowptr, col, key, lam, beaten, mark);
 }
 
-// Selection and marking of one round in one pass.  An undecided row that no
-// strong neighbour beat becomes C.  Otherwise it becomes F if a strong neighbour
-// is C, either decided earlier or selected in this round (undecided and not
-// beaten: its own thread may be writing C at the same time, and either value it
-// reads means C; a beaten one's may be writing F, and either means not C); rows
-// left undecided form the next round's list.  G lanes per row, NT-thread blocks, R
-// rows per thread and list reservation; the loop runs the same number of times on
-// every thread of a block, so all reach block_reserve_rows.
+// The mark pass of a round; rows left undecided form the next round's list.
+// NT-thread blocks, R rows per thread and list reservation; the loop runs the same
+// number of times on every thread of a block, so all reach block_reserve_rows.
 template <int G, int NT, int R>
 __global__ void __launch_bounds__(NT)
 k_pmis_mark_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
@@ -321,9 +360,7 @@ k_pmis_mark_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
                  int32_t* __restrict__ next, int* __restrict__ next_cnt) {
     constexpr int RPB = NT / G;   // rows per block and step
     const int c = *cnt;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane & (G - 1);
-    const int gbase = lane & ~(G - 1);
+    const int sub = threadIdx.x & (G - 1);
     const int stride = gridDim.x * RPB * R;
     for (int kb = blockIdx.x * RPB * R; kb < c; kb += stride) {
         int32_t row[R];
@@ -334,39 +371,53 @@ k_pmis_mark_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
             row[r] = k < c ? list[k] : -1;     // undecided at the start of the round
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int32_t i = row[r];
-            bool sel = false, f = false;
-            if (i >= 0) {
-                const int64_t rs = rowptr[i];
-                const int len = static_cast<int>(rowptr[i + 1] - rs);
-                sel = mark[i] != beaten;
-                for (int e = sub; e < len && !sel && !f; e += kPmisLoads * G) {
-                    int32_t j[kPmisLoads];
-                    uint8_t m[kPmisLoads];
-#pragma unroll
-                    for (int u = 0; u < kPmisLoads; ++u) j[u] = col[rs + min(e + u * G, len - 1)];
-#pragma unroll
-                    for (int u = 0; u < kPmisLoads; ++u) m[u] = mark[j[u]];
-#pragma unroll
-                    for (int u = 0; u < kPmisLoads; ++u) f |= m[u] != beaten && m[u] != kMarkF;
-                }
-            }
-            const uint64_t fm = __ballot(f);
-            const bool anyf = ((fm >> gbase) & ((G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull))) != 0;
-            const bool lead = i >= 0 && sub == 0;
-            if (lead && (sel || anyf)) {
-                mark[i] = sel ? kMarkC : kMarkF;
-                key[i] = 0;
-                state[i] = sel ? ST_C : ST_F;
-            }
-            if (lead && !sel && !anyf) keep |= 1u << r;
-        }
+        for (int r = 0; r < R; ++r)
+            if (pmis_mark_row<G>(row[r], sub, rowptr, col, beaten, state, key, mark)) keep |= 1u << r;
         int slot[R];
         block_reserve_rows<NT, R>(keep, next_cnt, slot);
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if ((keep >> r) & 1u) next[slot[r]] = row[r];
+    }
+}
+
+// The rounds that are left, in one block: on a short list a round costs two launches
+// of 4-5 us each whatever its length, and every third one a readback; here it costs
+// two block barriers (8^3 S2 solve 13.5 -> 13.0 ms).  Every round decides at least the undecided row of the largest
+// key, so the loop ends.  Limits of 1024 / 4096 / 16384 rows, cold sweeps: 20^3 tets S4
+// 16.12 / 16.04 / 16.18 ms (16.54 without), 64^3 S2 plain 31.7 / 31.7 / 32.0 (32.2).
+constexpr int kPmisFinish = 2048;
+constexpr int kFinishThreads = 1024;
+template <int G>
+__global__ void __launch_bounds__(kFinishThreads)
+k_pmis_finish(int32_t* list, int32_t* next, const int* __restrict__ cnt, const int64_t* __restrict__ rowptr,
+              const int32_t* __restrict__ col, uint64_t* key, const int* __restrict__ lam, uint8_t beaten,
+              int8_t* __restrict__ state, uint8_t* mark) {
+    constexpr int RPB = kFinishThreads / G;
+    __shared__ int s_n;
+    const int sub = threadIdx.x & (G - 1), lane = threadIdx.x & 63;
+    const int first = static_cast<int>(threadIdx.x) / G;
+    int n = *cnt;
+    while (n > 0) {
+        for (int k = first; k < n; k += RPB) pmis_compare_row<G>(list[k], sub, rowptr, col, key, lam, beaten, mark);
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+        for (int kb = 0; kb < n; kb += RPB) {
+            const int32_t i = kb + first < n ? list[kb + first] : -1;
+            const bool keep = pmis_mark_row<G>(i, sub, rowptr, col, beaten, state, key, mark);
+            const uint64_t m = __ballot(keep);
+            int base = 0;
+            if (lane == 0 && m) base = atomicAdd(&s_n, __popcll(m));
+            base = __shfl(base, 0, 64);
+            if (keep) next[base + __popcll(m & ((1ull << lane) - 1ull))] = i;
+        }
+        __syncthreads();
+        n = s_n;
+        int32_t* const t = list;
+        list = next;
+        next = t;
+        beaten = static_cast<uint8_t>(3 - beaten);
+        __syncthreads();       // s_n is read before the next round clears it
     }
 }
 
@@ -2946,6 +2997,13 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 PAIR_CHECK(round < 100000, "PMIS did not terminate");
                 const int nxt = cur ^ 1;
                 const uint8_t beaten = static_cast<uint8_t>(1 + (round & 1));
+                if (bound <= kPmisFinish) {
+                    hipLaunchKernelGGL(k_pmis_finish<kPmisG>, dim3(1), dim3(kFinishThreads), 0, s_, plist[cur].p,
+                                       plist[nxt].p, pcnt.p + cur, srp.p, scol.p, pkey.p, lam.p, beaten, state.p,
+                                       mark.p);
+                    PAIR_LAUNCH_CHECK();
+                    break;
+                }
                 const unsigned pg = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 256), 8192));
                 hipLaunchKernelGGL(k_pmis_compare_list<kPmisG>, dim3(pg), dim3(256), 0, s_, plist[cur].p,
                                    pcnt.p + cur, srp.p, scol.p, pkey.p, lam.p, beaten, mark.p, pcnt.p + nxt);

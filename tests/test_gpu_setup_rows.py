@@ -10,12 +10,12 @@ from tests.gpu_util import need_gpu
 pytestmark = pytest.mark.gpu
 
 
-def _check(A, seed=3):
+def _check(A, seed=3, coarse_max=8):
     from oracle import air_ref as AR
     from paper_1910_11463_amd.solver import Amg
-    one = AR.setup(A, AR.Options(coarse_max=8, seed=seed, max_levels=2))
+    one = AR.setup(A, AR.Options(coarse_max=coarse_max, seed=seed, max_levels=2))
     assert len(one) == 2
-    g = Amg(coarse_max=8, pmis_seed=seed, max_levels=2)
+    g = Amg(coarse_max=coarse_max, pmis_seed=seed, max_levels=2)
     g.setup(A.indptr, A.indices, A.data, None)
     got = g.level(0)
     g.close()
@@ -72,3 +72,12 @@ def test_hubs_beyond_the_packed_count(extra):
         assert L.cf[0] != L.cf[1]
         if m[0] != m[1]:
             assert (L.cf[0] > 0) == (m[0] > m[1])
+
+
+@pytest.mark.parametrize("n", [2, 511, 2048, 2049, 5000])
+def test_split_rounds_in_one_launch_and_in_lists(n):
+    """A random graph of n rows around the size at which one launch runs every
+    round, and above it, where only the last rounds do."""
+    need_gpu()
+    print("rows", n, flush=True)
+    _check(_of_lengths([min(n, 2 + i % 7) for i in range(n)], n), coarse_max=min(8, n // 2))
