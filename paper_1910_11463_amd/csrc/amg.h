@@ -329,6 +329,8 @@ public:
 // ---------------------------------------------------------------- primitives
 // Exclusive scan of n int64 counts into out[0..n] (out[n] = total); returns total.
 int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
+// The same of the flags in[i] == value.
+int64_t exclusive_count(const int8_t* in, int8_t value, int64_t* out, int64_t n, hipStream_t s);
 
 // Member id per row from the members' first rows (-1: absent) and rows on the
 // device; most: the largest member's rows.

@@ -462,23 +462,25 @@ k_classify(int64_t n, int mode, const int64_t* __restrict__ a, const int64_t* __
 }
 
 // Host side: classes of n rows (only rows with mask[i] != 0 when a mask is
-// given); counts[k] = rows in class k.
+// given); counts[k] = rows in class k.  zeroed: NC counters that hold zero, if the
+// caller has them.
 template <int NC>
 void classify(int64_t n, int mode, const int64_t* a, const int64_t* ub,
               const std::array<int64_t, NC - 1>& bounds, DBuf<int32_t> (&lists)[NC], int (&counts)[NC],
-              hipStream_t s, const uint8_t* mask = nullptr) {
+              hipStream_t s, const uint8_t* mask = nullptr, int* zeroed = nullptr) {
     RowClasses rc{};
     for (int k = 0; k < NC; ++k) {
         lists[k].alloc(static_cast<size_t>(std::max<int64_t>(n, 1)));
         rc.list[k] = lists[k].p;
         if (k < NC - 1) rc.bound[k] = bounds[k];
     }
-    DBuf<int> cnt(NC);
-    PAIR_HIP(hipMemsetAsync(cnt.p, 0, NC * sizeof(int), s));
+    DBuf<int> own(zeroed ? 0 : NC);
+    int* const cnt = zeroed ? zeroed : own.p;
+    if (!zeroed) PAIR_HIP(hipMemsetAsync(cnt, 0, NC * sizeof(int), s));
     hipLaunchKernelGGL(k_classify<NC>, dim3(grid_for(n, 256 * kRowsPT)), dim3(256), 0, s, n, mode, a, ub, rc,
-                       cnt.p, mask);
+                       cnt, mask);
     PAIR_LAUNCH_CHECK();
-    read_back(counts, cnt.p, NC, s);
+    read_back(counts, cnt, NC, s);
 }
 
 // mask[col[e]] = 1 for every entry (the rows a sparse matrix refers to)
@@ -493,11 +495,6 @@ __global__ void k_to_float(int64_t n, const double* __restrict__ src, float* __r
 }
 
 // ------------------------------------------------------------- coarse numbering
-__global__ void k_is_c(int64_t n, const int8_t* __restrict__ state, int64_t* __restrict__ flag) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) flag[i] = state[i] == ST_C ? 1 : 0;
-}
-
 __global__ void k_member_counts(int B, const int64_t* __restrict__ off,
                                 const int64_t* __restrict__ cnt, const int64_t* __restrict__ cidx,
                                 int64_t* __restrict__ nc) {
@@ -2926,7 +2923,6 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
 
     DBuf<int64_t> d_off(B_), d_cnt(B_), d_newoff(B_), d_nc(B_);
     DBuf<uint8_t> d_part(B_);
-    DBuf<int> d_counter(1);
 
     for (int l = 0;; ++l) {
         Level& L = levels_[l];
@@ -2961,9 +2957,20 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
 
         // strength + lambda (fused with 1/a_ii)
         DBuf<uint8_t> sflag(L.A.nnz);
-        DBuf<int> lam(n);
+        // lambda, the mask of A P's rows and the level's counters, zeroed at once (a
+        // clear is a launch of 4-5 us, and a small level had ten: 64^3 S2 plain cold
+        // sweep 31.3 -> 30.4 ms with the scans of one tile and the C points' numbers)
+        const int64_t ctr0 = (n + (n + 3) / 4 + 1) & ~int64_t(1);
+        DBuf<int> lam(ctr0 + 32);
+        uint8_t* const need = reinterpret_cast<uint8_t*>(lam.p + n);
+        int* const ctr = lam.p + ctr0;
+        unsigned long long* const cf_ctr = reinterpret_cast<unsigned long long*>(ctr);      // 4 of 64 bits
+        int* const pcnt = ctr + 8;                                                        // 2
+        int* const sing_ctr = ctr + 10;
+        int* const longest = ctr + 11;
+        int *const cls_r = ctr + 12, *const cls_a = ctr + 18, *const cls_c = ctr + 24;    // 6 each
         DBuf<int64_t> scnt(n), srp(n + 1);
-        PAIR_HIP(hipMemsetAsync(lam.p, 0, n * sizeof(int), s_));
+        PAIR_HIP(hipMemsetAsync(lam.p, 0, lam.bytes(), s_));
         hipLaunchKernelGGL(k_strength_fused<kRowG>, dim3(grid_for(n * kRowG, 256)), dim3(256), 0, s_, n,
                            L.A.rowptr.p, L.A.col.p, L.A.val.p, L.seg.p, d_part.p, prm_.theta,
                            prm_.eps_r, L.dinv.p, sflag.p, lam.p, scnt.p);
@@ -2982,10 +2989,8 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         DBuf<int32_t> plist[2];
         plist[0].alloc(n);
         plist[1].alloc(n);
-        DBuf<int> pcnt(2);
-        PAIR_HIP(hipMemsetAsync(pcnt.p, 0, 2 * sizeof(int), s_));
         hipLaunchKernelGGL(k_pmis_init_list, dim3(grid_for(n, 256 * kRowsPT)), dim3(256), 0, s_, n, L.seg.p,
-                           d_off.p, d_part.p, lam.p, l, prm_.seed, state.p, pkey.p, mark.p, plist[0].p, pcnt.p);
+                           d_off.p, d_part.p, lam.p, l, prm_.seed, state.p, pkey.p, mark.p, plist[0].p, pcnt);
         PAIR_LAUNCH_CHECK();
         {
             constexpr int kPmisG = 2;   // lanes per row (rows of ~13 entries: 2 beat 1, 4, 8, 16)
@@ -2999,23 +3004,23 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 const uint8_t beaten = static_cast<uint8_t>(1 + (round & 1));
                 if (bound <= kPmisFinish) {
                     hipLaunchKernelGGL(k_pmis_finish<kPmisG>, dim3(1), dim3(kFinishThreads), 0, s_, plist[cur].p,
-                                       plist[nxt].p, pcnt.p + cur, srp.p, scol.p, pkey.p, lam.p, beaten, state.p,
+                                       plist[nxt].p, pcnt + cur, srp.p, scol.p, pkey.p, lam.p, beaten, state.p,
                                        mark.p);
                     PAIR_LAUNCH_CHECK();
                     break;
                 }
                 const unsigned pg = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 256), 8192));
                 hipLaunchKernelGGL(k_pmis_compare_list<kPmisG>, dim3(pg), dim3(256), 0, s_, plist[cur].p,
-                                   pcnt.p + cur, srp.p, scol.p, pkey.p, lam.p, beaten, mark.p, pcnt.p + nxt);
+                                   pcnt + cur, srp.p, scol.p, pkey.p, lam.p, beaten, mark.p, pcnt + nxt);
                 const unsigned pgm = static_cast<unsigned>(std::min<int64_t>(grid_for(bound * kPmisG, 1024), 8192));
                 hipLaunchKernelGGL((k_pmis_mark_list<kPmisG, 256, 4>), dim3(pgm), dim3(256), 0, s_, plist[cur].p,
-                                   pcnt.p + cur, srp.p, scol.p, beaten, state.p, pkey.p, mark.p, plist[nxt].p,
-                                   pcnt.p + nxt);
+                                   pcnt + cur, srp.p, scol.p, beaten, state.p, pkey.p, mark.p, plist[nxt].p,
+                                   pcnt + nxt);
                 PAIR_LAUNCH_CHECK();
                 cur = nxt;
                 if (round % 3 == 2) {
                     int und = 0;
-                    read_back(&und, pcnt.p + cur, 1, s_);
+                    read_back(&und, pcnt + cur, 1, s_);
                     if (und == 0) break;
                     bound = und;
                 }
@@ -3023,10 +3028,8 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         }
 
         // coarse numbering and the members that continue
-        DBuf<int64_t> isc(n), cidx(n + 1);
-        hipLaunchKernelGGL(k_is_c, dim3(grid_for(n, 256)), dim3(256), 0, s_, n, state.p, isc.p);
-        PAIR_LAUNCH_CHECK();
-        exclusive_scan(isc.p, cidx.p, n, s_);
+        DBuf<int64_t> cidx(n + 1);
+        exclusive_count(state.p, ST_C, cidx.p, n, s_);
         hipLaunchKernelGGL(k_member_counts, dim3(grid_for(B_, 64)), dim3(64), 0, s_, B_, d_off.p,
                            d_cnt.p, cidx.p, d_nc.p);
         PAIR_LAUNCH_CHECK();
@@ -3064,13 +3067,11 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         PAIR_CHECK(total_c < (int64_t(1) << 31), "coarse level too large for int32 indices");
 
         {
-            DBuf<unsigned long long> cc(4);
-            PAIR_HIP(hipMemsetAsync(cc.p, 0, 4 * sizeof(unsigned long long), s_));
             const unsigned g = static_cast<unsigned>(std::min<int64_t>(grid_for(n, 256), 1024));
-            hipLaunchKernelGGL(k_cf_counts, dim3(g), dim3(256), 0, s_, n, L.A.rowptr.p, L.cf.p, cc.p);
+            hipLaunchKernelGGL(k_cf_counts, dim3(g), dim3(256), 0, s_, n, L.A.rowptr.p, L.cf.p, cf_ctr);
             PAIR_LAUNCH_CHECK();
             unsigned long long h[4];
-            read_back(h, cc.p, 4, s_);
+            read_back(h, cf_ctr, 4, s_);
             L.n_f = static_cast<int64_t>(h[0]);
             L.nnz_f = static_cast<int64_t>(h[1]);
             L.n_c = static_cast<int64_t>(h[2]);
@@ -3212,7 +3213,6 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                                 nair_olist.p + nair_oseg[st]);
             nair_scol.reset();
             nair_sval.reset();
-            PAIR_HIP(hipMemsetAsync(d_counter.p, 0, sizeof(int), s_));
         } else if (dist2) {
             // the patterns; then rows of K <= 64 by k_r_build (one wave, LDS), the
             // longer ones by k_r_dist2 (one block, dense system in global memory)
@@ -3222,17 +3222,15 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             PAIR_LAUNCH_CHECK();
             DBuf<int32_t> rl[5];
             int nrc[5];
-            DBuf<int> rsing(1);
-            PAIR_HIP(hipMemsetAsync(rsing.p, 0, sizeof(int), s_));
             // mode 1 classifies by K = row length of R - 1: K <= 8, 16, 32, 64, longer
-            classify<5>(total_c, 1, L.R.rowptr.p, nullptr, {8, 16, 32, 64}, rl, nrc, s_);
+            classify<5>(total_c, 1, L.R.rowptr.p, nullptr, {8, 16, 32, 64}, rl, nrc, s_, nullptr, cls_r);
             for (int c = 0; c < 4; ++c) {
                 const int nr = nrc[c];
                 if (nr == 0) continue;
                 const int rpw = 8 >> c;
                 const unsigned g = static_cast<unsigned>(std::min<int64_t>((nr + rpw - 1) / rpw, 1 << 20));
 #define PAIR_RB_ARGS nr, rl[c].p, c2f.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, sflag.p, L.cf.p, prm_.kmax, \
-                     L.R.rowptr.p, L.R.col.p, L.R.val.p, rsing.p, nullptr
+                     L.R.rowptr.p, L.R.col.p, L.R.val.p, sing_ctr, nullptr
                 if (c == 0) hipLaunchKernelGGL((k_r_build<8, true>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
                 else if (c == 1) hipLaunchKernelGGL((k_r_build<16, true>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
                 else if (c == 2) hipLaunchKernelGGL((k_r_build<32, true>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
@@ -3249,16 +3247,14 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 DBuf<double> work(static_cast<size_t>(gf) * static_cast<size_t>(slice));
                 hipLaunchKernelGGL(k_r_dist2<2>, dim3(gf), dim3(256), 0, s_, nrc[4], rl[4].p, c2f.p, L.A.rowptr.p,
                                    L.A.col.p, L.A.val.p, sflag.p, L.cf.p, nullptr, nullptr, L.R.rowptr.p, L.R.col.p,
-                                   L.R.val.p, work.p, d2ld, rsing.p);
+                                   L.R.val.p, work.p, d2ld, sing_ctr);
                 PAIR_LAUNCH_CHECK();
             }
-            PAIR_HIP(hipMemcpyAsync(d_counter.p, rsing.p, sizeof(int), hipMemcpyDeviceToDevice, s_));
         } else if (direct) {
             hipLaunchKernelGGL((k_r_direct<kDG, false>), dim3(gdir), dim3(64), 0, s_, static_cast<int>(total_c),
                                c2f.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, sflag.p, L.cf.p, prm_.kmax,
                                prm_.filter_r, nullptr, L.R.rowptr.p, L.R.col.p, L.R.val.p);
             PAIR_LAUNCH_CHECK();
-            PAIR_HIP(hipMemsetAsync(d_counter.p, 0, sizeof(int), s_));
         } else {
             // the patterns into R first (full occupancy: the gathers that select
             // them), then the local systems by size K: <= 8, <= 16, <= 32, <= 64
@@ -3282,9 +3278,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
             // unknowns (~6, ~4.75 and ~3.75 waves per SIMD)
             DBuf<int32_t> rl[6];
             int nrc[6];
-            DBuf<int> rsing(1);
-            PAIR_HIP(hipMemsetAsync(rsing.p, 0, sizeof(int), s_));
-            classify<6>(total_c, 1, L.R.rowptr.p, nullptr, {8, 12, 14, 16, 32}, rl, nrc, s_);
+            classify<6>(total_c, 1, L.R.rowptr.p, nullptr, {8, 12, 14, 16, 32}, rl, nrc, s_, nullptr, cls_r);
             for (int c = 0; c < 6; ++c) {
                 const int nr = nrc[c];
                 if (nr == 0) continue;
@@ -3295,7 +3289,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 const int ph = prof_begin(s_, PROF_RBUILD);
                 unsigned long long* pb = prof_dev_bytes(ph);
 #define PAIR_RB_ARGS nr, rl[c].p, c2f.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, sflag.p, L.cf.p, prm_.kmax, \
-                     L.R.rowptr.p, L.R.col.p, L.R.val.p, rsing.p, pb
+                     L.R.rowptr.p, L.R.col.p, L.R.val.p, sing_ctr, pb
                 if (c == 0) hipLaunchKernelGGL((k_r_build<8, true>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
                 else if (c == 1) hipLaunchKernelGGL((k_r_build<16, true, 12>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
                 else if (c == 2) hipLaunchKernelGGL((k_r_build<16, true, 14>), dim3(g), dim3(64), 0, s_, PAIR_RB_ARGS);
@@ -3316,21 +3310,16 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                     PAIR_LAUNCH_CHECK();
                 }
             }
-            PAIR_HIP(hipMemcpyAsync(d_counter.p, rsing.p, sizeof(int), hipMemcpyDeviceToDevice, s_));
         }
-        int nsing = 0;
-        d2h(&nsing, d_counter.p, 1, s_);
         if (prm_.filter_r > 0.0 && !direct && !nair)
             filter_restriction(L, c2f.p, total_c);   // direct and nAIR: filtered already
         int r_longest = 0;   // longest row of R when it can exceed RMAX (distance 2)
         if (dist2) {
             // rows of R longer than RMAX are staged in global memory by k_rap_global
-            DBuf<int> mx(1);
-            PAIR_HIP(hipMemsetAsync(mx.p, 0, sizeof(int), s_));
             hipLaunchKernelGGL(k_max_row_len, dim3(grid_for(total_c, 256)), dim3(256), 0, s_, total_c,
-                               L.R.rowptr.p, mx.p);
+                               L.R.rowptr.p, longest);
             PAIR_LAUNCH_CHECK();
-            read_back(&r_longest, mx.p, 1, s_);
+            read_back(&r_longest, longest, 1, s_);
         }
 
         // A P: merge the entries of each row of A that interpolate from the same
@@ -3340,15 +3329,13 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         DBuf<double> ap_val(L.A.nnz);
         DBuf<int> ap_len(n);
         {
-            DBuf<uint8_t> need(n);
-            PAIR_HIP(hipMemsetAsync(need.p, 0, n, s_));
             hipLaunchKernelGGL(k_mark_cols, dim3(grid_for(L.R.nnz, 256)), dim3(256), 0, s_, L.R.nnz,
-                               L.R.col.p, need.p);
+                               L.R.col.p, need);
             PAIR_LAUNCH_CHECK();
             // rows by length: <= 16, <= 32 (registers), <= 64, <= 2048 (LDS)
             DBuf<int32_t> al[5];
             int na[5];
-            classify<5>(n, 0, L.A.rowptr.p, nullptr, {16, 32, 64, 2048}, al, na, s_, need.p);
+            classify<5>(n, 0, L.A.rowptr.p, nullptr, {16, 32, 64, 2048}, al, na, s_, need, cls_a);
             PAIR_CHECK(na[4] == 0, "a row of a coarse operator has more than 2048 entries");
             if (na[0] > 0)
                 hipLaunchKernelGGL(k_ap_reg<16>, dim3(grid_for(static_cast<int64_t>(na[0]) * 16, 256)),
@@ -3377,7 +3364,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         // <= 128, <= 256, <= 1024, <= 2048 in LDS, the rest global
         DBuf<int32_t> lists[6];
         int lcount[6];
-        classify<6>(total_c, 2, nullptr, ub.p, {0, 128, 256, 1024, 2048}, lists, lcount, s_);
+        classify<6>(total_c, 2, nullptr, ub.p, {0, 128, 256, 1024, 2048}, lists, lcount, s_, nullptr, cls_c);
         // hash-table scratch for the global class: 2 * pow2(products) slots per row
         std::vector<int64_t> gscr_off_h;
         std::vector<int> gchunks;   // first rows of the global class's launches, then lcount[5]
@@ -3495,7 +3482,8 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
         C.col.alloc(C.nnz);
         C.val.alloc(C.nnz);
         run_rap(true, &C);
-        PAIR_HIP(hipStreamSynchronize(s_));
+        int nsing = 0;
+        read_back(&nsing, sing_ctr, 1, s_);
         PAIR_CHECK(nsing == 0, "singular local lAIR system in " + std::to_string(nsing) + " rows");
 
         coarse_setup(L, coarse_here);

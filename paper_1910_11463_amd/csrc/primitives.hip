@@ -150,18 +150,28 @@ constexpr int kScanTile = kScanBlock * kScanItems;
 // out[n] and to the host page.  Bound by its loads and stores (16 B per value);
 // a pass for the tiles' sums, one for their offsets and a wait per level before:
 // 14 M values 3 launches and 2 waits, now one each.
+// A single tile needs no status.  Value(in[i]) is what is summed.
+struct ScanValue {
+    __device__ int64_t operator()(int64_t v) const { return v; }
+};
+struct ScanEqual {
+    int8_t to;
+    __device__ int64_t operator()(int8_t v) const { return v == to ? 1 : 0; }
+};
+
+template <class T, class Value>
 __global__ void __launch_bounds__(kScanBlock)
-k_scan(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t n, int64_t ntiles,
+k_scan(const T* __restrict__ in, Value value, int64_t* __restrict__ out, int64_t n, int64_t ntiles,
        unsigned long long* __restrict__ status, int64_t* __restrict__ host_total) {
     __shared__ int64_t sh[kScanTile];
     __shared__ int64_t wsum[kScanBlock / 64];
     __shared__ int64_t s_before;
     __shared__ unsigned s_tile;
-    const int64_t tile = tile_ticket(reinterpret_cast<unsigned*>(status + ntiles), &s_tile);
+    const int64_t tile = ntiles > 1 ? tile_ticket(reinterpret_cast<unsigned*>(status + ntiles), &s_tile) : 0;
     const int64_t base = tile * kScanTile;
     for (int i = threadIdx.x; i < kScanTile; i += kScanBlock) {
         const int64_t g = base + i;
-        sh[i] = g < n ? in[g] : 0;
+        sh[i] = g < n ? value(in[g]) : 0;
     }
     __syncthreads();
     int64_t v[kScanItems];
@@ -182,7 +192,7 @@ k_scan(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t n, int
         total += wsum[w];
     }
     if (wid == 0) {
-        const int64_t before = tile_prefix(status, tile, total);
+        const int64_t before = ntiles > 1 ? tile_prefix(status, tile, total) : 0;
         if (lane == 0) {
             s_before = before;
             if (tile == ntiles - 1) {
@@ -201,9 +211,9 @@ k_scan(const int64_t* __restrict__ in, int64_t* __restrict__ out, int64_t n, int
         if (g < n) out[g] = sh[i];
     }
 }
-}  // namespace
 
-int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s) {
+template <class T, class Value>
+int64_t scan(const T* in, Value value, int64_t* out, int64_t n, hipStream_t s) {
     if (n <= 0) {
         int64_t z = 0;
         PAIR_HIP(hipMemcpyAsync(out, &z, sizeof(int64_t), hipMemcpyHostToDevice, s));
@@ -211,14 +221,23 @@ int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s
         return 0;
     }
     const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    DBuf<unsigned long long> status(ntiles + 1);
+    DBuf<unsigned long long> status(ntiles > 1 ? ntiles + 1 : 0);
     HBuf<int64_t> total(1);
-    PAIR_HIP(hipMemsetAsync(status.p, 0, status.bytes(), s));
-    hipLaunchKernelGGL(k_scan, dim3(static_cast<unsigned>(ntiles)), dim3(kScanBlock), 0, s, in, out, n, ntiles,
-                       status.p, total.p);
+    if (ntiles > 1) PAIR_HIP(hipMemsetAsync(status.p, 0, status.bytes(), s));
+    hipLaunchKernelGGL((k_scan<T, Value>), dim3(static_cast<unsigned>(ntiles)), dim3(kScanBlock), 0, s, in, value,
+                       out, n, ntiles, status.p, total.p);
     PAIR_LAUNCH_CHECK();
     PAIR_HIP(hipStreamSynchronize(s));
     return *total.p;
+}
+}  // namespace
+
+int64_t exclusive_scan(const int64_t* in, int64_t* out, int64_t n, hipStream_t s) {
+    return scan(in, ScanValue{}, out, n, s);
+}
+
+int64_t exclusive_count(const int8_t* in, int8_t value, int64_t* out, int64_t n, hipStream_t s) {
+    return scan(in, ScanEqual{value}, out, n, s);
 }
 
 // ---------------------------------------------------------------- segments
