@@ -1909,8 +1909,8 @@ bool Hierarchy::solve_in(void* scratch, bool x_is_zero) {
     bool ok = false;
     try {
         // every entry the kernels read before writing: the member offsets and
-        // counts; norms, flags and counters are written by k_norm_finalize /
-        // k_zero_int before they are read
+        // counts; norms, flags and counters are written by k_norm_finalize
+        // before they are read
         h2d(sv_.moff, levels_[0].off.data(), B_, s_);
         h2d(sv_.mcnt, levels_[0].cnt.data(), B_, s_);
         ProfSuspend no_records;
