@@ -81,3 +81,28 @@ def test_split_rounds_in_one_launch_and_in_lists(n):
     need_gpu()
     print("rows", n, flush=True)
     _check(_of_lengths([min(n, 2 + i % 7) for i in range(n)], n), coarse_max=min(8, n // 2))
+
+
+@pytest.mark.parametrize("n,longest", [(17, 9), (2047, 16), (2049, 16), (4500, 16), (4500, 17)])
+def test_coarse_operator_of_packed_rows(n, longest):
+    """Rows of A P one after the other (no row of more than 16 entries; with one of 17
+    they stay at their rows' places): the Galerkin operator's pattern exact, its values
+    within 1e-12 of the largest, the bound of the hierarchy parity tests.  Every third
+    row couples to nothing and is referred to by few rows, so that rows of A P that
+    nothing needs lie between."""
+    need_gpu()
+    from oracle import air_ref as AR
+    from paper_1910_11463_amd.solver import Amg
+    print("packed rows", n, longest, flush=True)
+    lens = [1 if i % 3 == 0 else min(n, 2 + i % 15) for i in range(n)]
+    lens[n // 2] = min(n, longest)
+    A = _of_lengths(lens, n)
+    one = AR.setup(A, AR.Options(coarse_max=4, seed=3, max_levels=2))
+    assert len(one) == 2 and np.diff(A.indptr).max() == max(16, longest)
+    g = Amg(coarse_max=4, pmis_seed=3, max_levels=2)
+    g.setup(A.indptr, A.indices, A.data, None)
+    got = g.level(1)
+    g.close()
+    ref = one[1].A
+    assert np.array_equal(got["rowptr"], ref.indptr) and np.array_equal(got["col"], ref.indices)
+    assert np.abs(got["val"] - ref.data).max() <= 1e-12 * np.abs(ref.data).max()
