@@ -185,6 +185,16 @@ constexpr int kTailLevels = 32;                // options.max_levels <= 32
 // 400 / 1024 / 2048: an 8^3 S2 sweep (1357 rows, 8 members) 925 / 918 / 912 us
 // (1088 without), a 24^3 tet S4 solve 125.7 / 125.7 / 124.4 ms (125.7 without).
 constexpr int64_t kTailRows = 2048;
+// Entries (padded) of A and of R of a member on a tail level, at most: one workgroup
+// gathers all of them in LDS in every pass (11000 cycles for 27000), which a launch
+// over the whole chip does not feel.  By the member alone, not by how many share the
+// launch, so that it rounds the same in any batch.  Single matrices, us per cycle
+// without tail / limits of 32768, 40960, 49152 / no limit, levels below the finest:
+// 666 and 176 rows of 20600 and 26000 entries 91.9 / 91.9, 88.9, 88.4 / 88.9;
+// 550 and 173 of 36400 and 29700 97.2 / 96.9, 97.0, 98.8 / 99.6; 610 and 212 of 49800
+// and 44800 103.5 / - / 111.6; 417 and 146 of 97100 and 21300 107.8 / - / 125.6.
+// 24 such of 791 and 219 rows of 24600 and 37700: 133.1 / 133.9, 134.0, 128.9 / 130.3.
+constexpr int kTailEntries = 49152;
 constexpr size_t kTailLds = 150 * 1024;        // of the CU's 160 KB
 
 // A member's state after a convergence test, in pinned host memory.

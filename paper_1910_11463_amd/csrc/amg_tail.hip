@@ -1,6 +1,6 @@
 // The small levels of a V-cycle in one launch: one workgroup takes a member
-// (direction) from the first level on which it has at most kTailRows rows down to
-// its coarsest level and up again.
+// (direction) from the first level on which it has at most kTailRows rows, there and
+// further down at most kTailEntries entries, down to its coarsest level and up again.
 //
 // What bounds it: a small level's half-sweep, residual, restriction or
 // interpolation costs 3-4 us as a launch of its own whatever its size, about six
@@ -19,7 +19,7 @@
 //
 // A row is summed in the order of its entries, which differs from the level
 // kernels' order; whether a member's level is in the tail depends on that
-// member's rows alone, so a member rounds the same alone and in a batch.
+// member's rows and entries alone, so a member rounds the same alone and in a batch.
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -142,6 +142,7 @@ __global__ void __launch_bounds__(kPlanThreads)
 k_tail_fill(const TailTask* __restrict__ tasks, const int* __restrict__ count, const int* __restrict__ entry,
             const uint16_t* __restrict__ perm, int2* __restrict__ slices, double* __restrict__ val,
             uint16_t* __restrict__ col, double* __restrict__ dinv, int16_t* __restrict__ interp) {
+    if (entry[blockIdx.x] < 0) return;      // its level stays with the level kernels
     const TailTask T = tasks[blockIdx.x];
     const auto rp = (Global<int64_t>)T.rowptr;
     const auto tc = (Global<int32_t>)T.col;
@@ -399,11 +400,7 @@ void Hierarchy::build_tail() {
             lds = std::max(lds, need);
         }
     }
-    // the level kernels' members: those whose tail starts further down
-    level_on_.assign(nl, 0);
-    for (int b = 0; b < B_; ++b)
-        for (int l = 0; l + 1 < nlev_[b]; ++l)
-            if (first[b] < 0 || l < first[b]) level_on_[l] = 1;
+    level_on_.assign(nl, 1);
     for (int l = 0; l < nl; ++l) levels_[l].coarse_launch = static_cast<int>(levels_[l].coarse_members.size());
     if (lds == 0) return;
 
@@ -471,12 +468,10 @@ void Hierarchy::build_tail() {
             lev.push_back(q);
         }
     }
-    if (nperm >= (int64_t(1) << 31)) {             // place numbers are 32-bit
-        level_on_.assign(nl, 1);
-        return;
-    }
     const int nt = static_cast<int>(tasks.size());
-    std::vector<int> cnt(3 * static_cast<size_t>(nt), 0), entry(nt, 0);
+    // place numbers are 32-bit
+    if (nperm >= (int64_t(1) << 31) || nt >= (int64_t(1) << 31) / (kTailEntries / 64)) return;
+    std::vector<int> cnt(3 * static_cast<size_t>(nt), 0), entry(nt, -1);
     tail_perm_.alloc(std::max<int64_t>(nperm, 1));
     tail_slice_.alloc(std::max<int64_t>(nslice, 1));
     tail_dinv_.alloc(std::max<int64_t>(nrows, 1));
@@ -490,12 +485,36 @@ void Hierarchy::build_tail() {
                            cnt_d.p);
         PAIR_LAUNCH_CHECK();
         read_back(cnt.data(), cnt_d.p, cnt.size(), s_);
-        for (int k = 0; k < nt; ++k) {
+    }
+    // a member's levels from its coarsest up to the first whose A or R has too many
+    // entries; tasks are A and R of its levels in order
+    lds = 0;
+    int task = 0;
+    for (int b = 0; b < B_; ++b) {
+        if (first[b] < 0) continue;
+        const int last = nlev_[b] - 1, skip_to = task + 2 * (last - first[b]);
+        int l = last, k = skip_to;
+        while (l > first[b] && std::max(cnt[3 * (k - 2) + 2], cnt[3 * (k - 1) + 2]) <= kTailEntries / 64) {
+            --l;
+            k -= 2;
+        }
+        members[b].x += l - first[b];
+        members[b].y = last - l + 1;
+        first[b] = l;
+        for (; k < skip_to; ++k) {
             entry[k] = static_cast<int>(slots);
             slots += cnt[3 * k + 2];
-            PAIR_CHECK(slots < (int64_t(1) << 31), "coarse levels too large");
         }
+        task = skip_to;
+        std::vector<int64_t> n;
+        for (; l <= last; ++l) n.push_back(levels_[l].cnt[b]);
+        lds = std::max(lds, tail_lds(n));
     }
+    // the level kernels' members: those whose tail starts further down
+    level_on_.assign(nl, 0);
+    for (int b = 0; b < B_; ++b)
+        for (int l = 0; l + 1 < nlev_[b]; ++l)
+            if (first[b] < 0 || l < first[b]) level_on_[l] = 1;
     tail_val_.alloc(std::max<int64_t>(64 * slots, 1));
     tail_col_.alloc(std::max<int64_t>(64 * slots, 1));
     if (nt > 0) {

@@ -82,3 +82,50 @@ def test_members_of_every_size(pre, post, fp32):
         assert np.abs(y - ref).max() <= 1e-11 * 5 * 48 * max(1.0, np.abs(b[s]).max()) + 1e-13
         one.close()
     a.close()
+
+
+def _even(n, m, seed):
+    """As _matrix, every row with m random columns."""
+    rng = np.random.default_rng(seed)
+    A = np.zeros((n, n))
+    A[np.arange(n)[:, None], rng.integers(0, n, (n, m))] = -rng.uniform(0.1, 1.0, (n, m))
+    np.fill_diagonal(A, 0.0)
+    A *= 0.8 / np.abs(A).sum(1, keepdims=True)
+    np.fill_diagonal(A, 1.0)
+    rows, cols = np.nonzero(A)
+    return np.concatenate([[0], np.cumsum(np.bincount(rows))]).astype(np.int64), cols.astype(np.int32), A[rows, cols]
+
+
+@pytest.mark.parametrize("n,m,long_rows", [(2000, 3, False), (3000, 20, True)])
+def test_levels_of_long_rows_stay_with_the_level_kernels(n, m, long_rows):
+    """A member whose first coarse level has some 400 rows of over 200 entries: its
+    half-sweeps there are launches of their own (one workgroup takes longer), those of a
+    member of short rows are not; alone, beside another and against the dense solution
+    (bound as above, with sqrt(3000) = 55)."""
+    import ctypes
+    need_gpu()
+    from paper_1910_11463_amd import binding as B
+    from paper_1910_11463_amd.solver import Amg
+    mat = _even(n, m, n)
+    opts = dict(tol_inner=1e-11, max_inner=400, use_graph=0)
+    b = np.random.default_rng(9).uniform(-1.0, 1.0, n)
+    one = Amg(**opts)
+    one.setup(*mat)
+    L1 = one.level(1)
+    print("first coarse level", len(L1["rowptr"]) - 1, len(L1["col"]), flush=True)
+    assert len(L1["rowptr"]) - 1 <= 2048 and (len(L1["col"]) > 60000) == long_rows
+    B.check(B.pair_profile_enable(1))
+    y, it, rel, rc = one.solve(b)
+    k, ms, by = ctypes.c_int64(), ctypes.c_double(), ctypes.c_double()
+    B.check(B.pair_profile_read(3, ctypes.byref(k), ctypes.byref(ms), ctypes.byref(by)))
+    B.check(B.pair_profile_enable(0))
+    one.close()
+    assert rc == 0, rel
+    assert (k.value > 0) == long_rows
+    assert np.abs(y - np.linalg.solve(_dense(mat), b)).max() <= 1e-11 * 5 * 55 * max(1.0, np.abs(b).max()) + 1e-13
+    rowptr, col, val, seg = _batch([_even(700, 4, 7), mat])
+    a = Amg(**opts)
+    a.setup(rowptr, col, val, seg)
+    x, it2, _, rc2 = a.solve(np.concatenate([np.ones(700), b]))
+    a.close()
+    assert rc2 == 0 and it2[1] == it[0] and np.array_equal(x[700:], y)
