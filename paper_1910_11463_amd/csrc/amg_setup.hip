@@ -386,7 +386,12 @@ k_pmis_mark_list(const int32_t* __restrict__ list, const int* __restrict__ cnt,
 // two block barriers (8^3 S2 solve 13.5 -> 13.0 ms).  Every round decides at least the undecided row of the largest
 // key, so the loop ends.  Limits of 1024 / 4096 / 16384 rows, cold sweeps: 20^3 tets S4
 // 16.12 / 16.04 / 16.18 ms (16.54 without), 64^3 S2 plain 31.7 / 31.7 / 32.0 (32.2).
+// Their strong entries, by the level's mean row, are limited too, for one block reads
+// them all.  Setups of random graphs, us without / limits of 512, 1024, 2048 rows: 2000
+// rows of 10 entries 2623 / 2426, 2457, 2446; of 20 6696 / 6492, 6453, 6530; of 40
+// 4571 / 4451, 4437, 4527; of 100 3469 / 3365, 3386, 3556; of 200 5455 / 5366, 5388, 5710.
 constexpr int kPmisFinish = 2048;
+constexpr int64_t kPmisFinishEntries = 32768;
 constexpr int kFinishThreads = 1024;
 template <int G>
 __global__ void __launch_bounds__(kFinishThreads)
@@ -3063,7 +3068,7 @@ void Hierarchy::setup(Csr&& A0, const std::vector<int64_t>& off0, const std::vec
                 PAIR_CHECK(round < 100000, "PMIS did not terminate");
                 const int nxt = cur ^ 1;
                 const uint8_t beaten = static_cast<uint8_t>(1 + (round & 1));
-                if (bound <= kPmisFinish) {
+                if (bound <= kPmisFinish && bound * nstrong <= kPmisFinishEntries * n) {
                     hipLaunchKernelGGL(k_pmis_finish<kPmisG>, dim3(1), dim3(kFinishThreads), 0, s_, plist[cur].p,
                                        plist[nxt].p, pcnt + cur, srp.p, scol.p, pkey.p, lam.p, beaten, state.p,
                                        mark.p);

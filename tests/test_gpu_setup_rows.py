@@ -106,3 +106,13 @@ def test_coarse_operator_of_packed_rows(n, longest):
     ref = one[1].A
     assert np.array_equal(got["rowptr"], ref.indptr) and np.array_equal(got["col"], ref.indices)
     assert np.abs(got["val"] - ref.data).max() <= 1e-12 * np.abs(ref.data).max()
+
+
+@pytest.mark.parametrize("n,row", [(2048, 5), (2048, 60), (500, 90), (700, 50), (700, 55), (700, 60)])
+def test_split_rounds_of_short_lists_with_long_rows(n, row):
+    """Lists short enough for one launch, with few and with many strong entries (the
+    limit of 32768 lies at about 47 of a row's strong entries for 700 rows, of which the
+    random values leave five in six): list rounds first, then one launch."""
+    need_gpu()
+    print("rows", n, "of", row, flush=True)
+    _check(_of_lengths([row] * n, n + row))
