@@ -111,8 +111,8 @@ def test_coarse_operator_of_packed_rows(n, longest):
 @pytest.mark.parametrize("n,row", [(2048, 5), (2048, 60), (500, 90), (700, 50), (700, 55), (700, 60)])
 def test_split_rounds_of_short_lists_with_long_rows(n, row):
     """Lists short enough for one launch, with few and with many strong entries (the
-    limit of 32768 lies at about 47 of a row's strong entries for 700 rows, of which the
-    random values leave five in six): list rounds first, then one launch."""
+    limit of 32768 lies between 55 and 60 entries for 700 rows, five in six of them
+    strong): list rounds first, then one launch."""
     need_gpu()
     print("rows", n, "of", row, flush=True)
     _check(_of_lengths([row] * n, n + row))
