@@ -243,8 +243,10 @@ public:
     // hipGraphs (one for a first cycle from x = 0, one for every other cycle),
     // each the second time that kind of cycle is needed, and replays them from
     // then on; the graphs stay with the hierarchy.
+    // b_may_be_zero: from x = 0, the members' state is read before the first cycle,
+    // which is launched only if some member needs it; otherwise it is launched at once.
     // Returns true if all members converged.
-    bool solve(bool use_graph, bool x_is_zero);
+    bool solve(bool use_graph, bool x_is_zero, bool b_may_be_zero = true);
     // The same V-cycles with the per-member scratch in the caller's device
     // region `scratch` of at least solve_scratch_bytes() bytes (256-byte
     // aligned): no device memory is allocated and no graph is used; the region
@@ -300,7 +302,7 @@ private:
     std::vector<Level> levels_;
     std::vector<int> nlev_;
     SolveView carve_solve_scratch(void* base) const;
-    bool solve_impl(bool use_graph, bool x_is_zero);
+    bool solve_impl(bool use_graph, bool x_is_zero, bool b_may_be_zero);
 
     SolveBufs sb_;
     SolveView sv_;                    // the scratch the solve kernels use

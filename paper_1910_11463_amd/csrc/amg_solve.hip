@@ -1866,7 +1866,9 @@ void Hierarchy::launch_cycle_and_test(bool x_is_zero, int /*it_offset*/) {
     PAIR_LAUNCH_CHECK();
 }
 
-bool Hierarchy::solve(bool use_graph, bool x_is_zero) { return solve_impl(use_graph, x_is_zero); }
+bool Hierarchy::solve(bool use_graph, bool x_is_zero, bool b_may_be_zero) {
+    return solve_impl(use_graph, x_is_zero, b_may_be_zero);
+}
 
 namespace {
 constexpr size_t kAlign = 256;
@@ -1914,7 +1916,7 @@ bool Hierarchy::solve_in(void* scratch, bool x_is_zero) {
         h2d(sv_.moff, levels_[0].off.data(), B_, s_);
         h2d(sv_.mcnt, levels_[0].cnt.data(), B_, s_);
         ProfSuspend no_records;
-        ok = solve_impl(false, x_is_zero);
+        ok = solve_impl(false, x_is_zero, true);
     } catch (...) {
         sv_ = own;
         throw;
@@ -1923,7 +1925,7 @@ bool Hierarchy::solve_in(void* scratch, bool x_is_zero) {
     return ok;
 }
 
-bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
+bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero, bool b_may_be_zero) {
     Level& L0 = levels_[0];
     // |b| per member and the initial state
     dispatch_lpr(L0.lpr, [&](auto lc) {
@@ -1960,9 +1962,10 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero) {
         for (int b = 0; b < B_; ++b) n += sb_.result.p[b].active;
         return n;
     };
-    // from x = 0 every member with b != 0 needs a cycle, so the first one is
-    // launched without looking (a cycle with no active member changes nothing)
-    int n_act = x_is_zero ? 1 : wait();
+    // from x = 0 every member with b != 0 needs a cycle, so where b is expected to be
+    // nonzero the first one is launched without looking (a cycle with no active member
+    // changes nothing, but costs its launches and a wait)
+    int n_act = x_is_zero && !b_may_be_zero ? 1 : wait();
 
     int cycles = 0;
     bool first = true;

@@ -417,6 +417,7 @@ int pair_set_materials(pair_ctx* ctx, const double* sigma_t, const double* sigma
             PAIR_CHECK(std::isfinite(qq[e]), "q must be finite");
         }
         const bool st_changed = !c.have_mats || c.sigt_h != st;
+        c.q_nonzero = std::any_of(qq.begin(), qq.end(), [](double v) { return v != 0.0; });
         c.sigt.alloc(E);
         c.sigs.alloc(E);
         c.q.alloc(E);
@@ -446,6 +447,7 @@ int pair_set_dual_source(pair_ctx* ctx, const double* src, int per_direction, in
         const size_t n = static_cast<size_t>(c.N()) * (per_direction ? c.M : 1);
         to_device(c.ext, src, n, where, c.s);
         PAIR_HIP(hipStreamSynchronize(c.s));
+        c.ext_nonzero = !per_direction && c.any_nonzero(c.ext.p);
         c.ext_per_dir = per_direction != 0;
         c.have_ext = true;
         c.psi_valid = false;
@@ -521,11 +523,7 @@ int pair_transport_sweep(pair_ctx* ctx, int mode, const double* phi_in, double* 
         if (phi_in) to_device(phin, phi_in, N, where, c.s);
         if (!c.psi.p || c.psi.n != static_cast<size_t>(c.M) * N) c.psi.alloc(static_cast<size_t>(c.M) * N);
         if (!c.phi.p || c.phi.n != static_cast<size_t>(N)) c.phi.alloc(N);
-        SourceSpec src;
-        src.q = c.q.p;
-        src.ext = c.have_ext ? c.ext.p : nullptr;
-        src.ext_per_dir = c.ext_per_dir;
-        src.inflow = c.have_inflow ? c.inflow.p : nullptr;
+        const SourceSpec src = c.source();
         bool ok = c.sweep(mode, src, phin.p, c.psi.p, c.phi.p, st, false);
         c.psi_valid = true;
         if (psi_out) from_device(psi_out, c.psi.p, static_cast<size_t>(c.M) * N, where, c.s);
@@ -614,11 +612,7 @@ int pair_solve(pair_ctx* ctx, int mode, const double* phi0, double* phi_out, dou
         const int64_t N = c.N();
         DBuf<double> phi0d;
         if (phi0) to_device(phi0d, phi0, N, where, c.s);
-        SourceSpec src;
-        src.q = c.q.p;
-        src.ext = c.have_ext ? c.ext.p : nullptr;
-        src.ext_per_dir = c.ext_per_dir;
-        src.inflow = c.have_inflow ? c.inflow.p : nullptr;
+        const SourceSpec src = c.source();
         rc = solve_impl(c, mode, src, phi0d.p, c.psi, c.phi, st);
         from_device(phi_out, c.phi.p, N, where, c.s);
         if (psi_out) from_device(psi_out, c.psi.p, static_cast<size_t>(c.M) * N, where, c.s);
@@ -665,6 +659,7 @@ int pair_adjoint(pair_ctx* ctx, int mode, const double* grad_phi, double* dJ_dsi
         src.q = nullptr;
         src.ext = g.p;
         src.ext_per_dir = false;
+        src.nonzero = c.any_nonzero(g.p);
         DBuf<double> psi_a, phi_a;
         // the adjoint iteration starts cold (warm start would read the forward psi)
         const int warm = c.opt.warm_start;
@@ -743,11 +738,7 @@ int pair_export_fine_operator(pair_ctx* ctx, int m, int64_t* nnz, int64_t* rowpt
             d2h(val, A.val.p, A.nnz, c.s);
         }
         if (b) {
-            SourceSpec src;
-            src.q = c.q.p;
-            src.ext = c.have_ext ? c.ext.p : nullptr;
-            src.ext_per_dir = c.ext_per_dir;
-            src.inflow = c.have_inflow ? c.inflow.p : nullptr;
+            const SourceSpec src = c.source();
             DBuf<double> tmp(N);
             c.rhs_batch(bt, src, nullptr, tmp.p, c.s);
             d2h(b, tmp.p, N, c.s);

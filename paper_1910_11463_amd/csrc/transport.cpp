@@ -51,6 +51,22 @@ void Context::check_ready() const {
     if (!have_mats) throw Error(E_STATE, "no materials set");
 }
 
+SourceSpec Context::source() const {
+    SourceSpec src;
+    src.q = q.p;
+    src.ext = have_ext ? ext.p : nullptr;
+    src.ext_per_dir = ext_per_dir;
+    src.inflow = have_inflow ? inflow.p : nullptr;
+    src.nonzero = q_nonzero || (have_ext && ext_nonzero);
+    return src;
+}
+
+bool Context::any_nonzero(const double* v) {
+    if (!norms.p) norms.alloc(2);
+    diff_norms(N(), v, v, norms.p, s);
+    return !(norms.p[1] == 0.0);
+}
+
 AmgParams params_from_options(const pair_options& o) {
     AmgParams p;
     p.theta = o.theta;
@@ -344,7 +360,7 @@ bool Context::sweep(int mode, const SourceSpec& src, const double* phi_in, doubl
         bool ok;
         {
             TraceRange tr("pair batch solve");
-            ok = bt.H->solve(opt.use_graph != 0, !use_warm);
+            ok = bt.H->solve(opt.use_graph != 0, !use_warm, !src.nonzero);
         }
         const double t3 = now_ms();
         for (int b = 0; b < B; ++b) {

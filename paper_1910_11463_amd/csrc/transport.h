@@ -54,6 +54,8 @@ struct SourceSpec {
     const double* ext = nullptr;      // dual-space source (device) or null
     bool ext_per_dir = false;         // ext is [M][N] instead of [N]
     const double* inflow = nullptr;   // nodal inflow data [M][N] (device) or null (vacuum)
+    bool nonzero = false;             // q or a shared ext is not all zero: no direction's
+                                      // right-hand side is expected to be zero
 };
 
 struct Context {
@@ -73,9 +75,11 @@ struct Context {
     DBuf<double> sigt, sigs, q;
     std::vector<double> sigt_h;
     bool have_mats = false;
+    bool q_nonzero = false;             // some element has a source
 
     DBuf<double> ext;                   // dual source
     bool ext_per_dir = false;
+    bool ext_nonzero = false;           // ext is shared by the directions and not all zero
     bool have_ext = false;
 
     DBuf<double> inflow;                // [M][N] nodal inflow values (zero: vacuum)
@@ -112,6 +116,9 @@ struct Context {
 
     // building blocks
     void check_ready() const;
+    SourceSpec source() const;          // of the forward problem
+    // v [N] (device) holds a nonzero value; waits for the stream
+    bool any_nonzero(const double* v);
     void build_batches(int mode, pair_stats* st);
     Csr assemble_fine(Batch& b, hipStream_t st, double* t_assemble_ms);
     void assemble_batch(Batch& b, hipStream_t st, double* t_assemble_ms);
