@@ -9,6 +9,8 @@
 #include <string>
 #include <vector>
 
+#include "pinned_pool.h"
+
 namespace pair {
 
 // ---------------------------------------------------------------- errors
@@ -110,9 +112,9 @@ inline void d2d(T* dst, const T* src, size_t n, hipStream_t s) {
 
 // Pinned host memory that kernels write results to (a device copy into pageable
 // memory costs 12 us over the kernel and the wait for it, a store to a pinned
-// page nothing measurable).  Freed blocks are kept for the next owner and given
-// back by pool_release_all(); an owner frees its block only after the kernels
-// that write it are done.
+// page nothing measurable).  Freed blocks are kept for the next owner within
+// PinnedPool's limits and given back by pool_release_all(); an owner frees its block
+// only after the kernels that write it are done.
 void* pinned_alloc(size_t bytes);
 void pinned_free(void* p);
 
@@ -137,9 +139,15 @@ struct HBuf {
     }
 };
 
-// Copies n values to the host through pinned memory and waits for the stream.
+// Copies n values to the host and waits for the stream; through pinned memory where
+// they fit a block that is kept (locking pages for one copy costs more than it saves).
 template <class T>
 inline void read_back(T* h, const T* d, size_t n, hipStream_t s) {
+    if (n * sizeof(T) > kPinnedBlock) {
+        d2h(h, d, n, s);
+        PAIR_HIP(hipStreamSynchronize(s));
+        return;
+    }
     HBuf<T> pin(n);
     if (n) PAIR_HIP(hipMemcpyAsync(pin.p, d, n * sizeof(T), hipMemcpyDeviceToHost, s));
     PAIR_HIP(hipStreamSynchronize(s));

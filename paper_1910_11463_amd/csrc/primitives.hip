@@ -6,6 +6,7 @@
 
 #include "amg.h"
 #include "kernels_common.h"
+#include "pinned_pool.h"
 
 namespace pair {
 
@@ -15,13 +16,18 @@ struct Block {
     size_t size;
     hipStream_t stream;
 };
+void* pinned_malloc(size_t bytes) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocCoherent) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
 struct Pool {
     std::mutex mu;
     std::multimap<std::pair<hipStream_t, size_t>, void*> free_blocks;   // (stream, size) -> ptr
     std::unordered_map<void*, Block> live;
     size_t in_use = 0;
-    std::multimap<size_t, void*> pinned_free;       // size -> ptr
-    std::unordered_map<void*, size_t> pinned_live;
+    PinnedPool pinned{pinned_malloc, [](void* p) { (void)hipHostFree(p); }};
 };
 Pool& pool() {
     static Pool* p = new Pool();   // intentionally leaked: outlives static destructors
@@ -106,36 +112,16 @@ void pool_release_all() {
     std::lock_guard<std::mutex> g(P.mu);
     for (auto& kv : P.free_blocks) (void)hipFree(kv.second);
     P.free_blocks.clear();
-    for (auto& kv : P.pinned_free) (void)hipHostFree(kv.second);
-    P.pinned_free.clear();
+    P.pinned.release();
 }
 
 void* pinned_alloc(size_t bytes) {
-    Pool& P = pool();
-    const size_t sz = std::max<size_t>(4096, round_size(bytes));
-    std::lock_guard<std::mutex> g(P.mu);
-    auto it = P.pinned_free.find(sz);
-    void* p = nullptr;
-    if (it != P.pinned_free.end()) {
-        p = it->second;
-        P.pinned_free.erase(it);
-    } else if (hipHostMalloc(&p, sz, hipHostMallocCoherent) != hipSuccess) {
-        (void)hipGetLastError();
-        throw Error(E_OOM, "pinned host allocation of " + std::to_string(sz) + " bytes failed");
-    }
-    P.pinned_live[p] = sz;
+    void* p = pool().pinned.get(bytes);
+    if (!p) throw Error(E_OOM, "pinned host allocation of " + std::to_string(bytes) + " bytes failed");
     return p;
 }
 
-void pinned_free(void* p) {
-    if (!p) return;
-    Pool& P = pool();
-    std::lock_guard<std::mutex> g(P.mu);
-    auto it = P.pinned_live.find(p);
-    if (it == P.pinned_live.end()) return;
-    P.pinned_free.emplace(it->second, p);
-    P.pinned_live.erase(it);
-}
+void pinned_free(void* p) { pool().pinned.put(p); }
 
 size_t pool_bytes_in_use() { return pool().in_use; }
 
