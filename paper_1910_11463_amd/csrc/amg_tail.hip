@@ -404,6 +404,15 @@ void Hierarchy::build_tail() {
     for (int l = 0; l < nl; ++l) levels_[l].coarse_launch = static_cast<int>(levels_[l].coarse_members.size());
     if (lds == 0) return;
 
+    // place of every member's inverse on its coarsest level
+    std::vector<int64_t> inv_off(B_, 0);
+    for (const Level& L : levels_) {
+        int64_t o = 0;
+        for (int b : L.coarse_members) {
+            inv_off[b] = o;
+            o += L.cnt[b] * L.cnt[b];
+        }
+    }
     std::vector<TailTask> tasks;
     std::vector<TailLevel> lev;
     std::vector<int2> members(B_, make_int2(0, 0));
@@ -458,12 +467,7 @@ void Hierarchy::build_tail() {
                 tasks.push_back(Rt);
                 nrows += q.n;
             } else {
-                int64_t o = 0;
-                for (int k : L.coarse_members) {
-                    if (k == b) break;
-                    o += L.cnt[k] * L.cnt[k];
-                }
-                q.inv = L.coarse_inv.p + o;
+                q.inv = L.coarse_inv.p + inv_off[b];
             }
             lev.push_back(q);
         }
@@ -541,16 +545,13 @@ void Hierarchy::build_tail() {
     std::vector<std::vector<int64_t>> moff(nl), mn(nl), ioff(nl);
     for (int l = 0; l < nl; ++l) {
         Level& L = levels_[l];
-        int64_t o = 0;
-        for (int b : L.coarse_members) {
+        for (int b : L.coarse_members)
             if (first[b] < 0) {
                 mem[l].push_back(b);
                 moff[l].push_back(L.off[b]);
                 mn[l].push_back(L.cnt[b]);
-                ioff[l].push_back(o);
+                ioff[l].push_back(inv_off[b]);
             }
-            o += L.cnt[b] * L.cnt[b];
-        }
         L.coarse_launch = static_cast<int>(mem[l].size());
         bool relax = false;
         for (int b = 0; b < B_; ++b)
