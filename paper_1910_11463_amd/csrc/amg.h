@@ -179,6 +179,10 @@ struct Level {
 
 // The small levels of a V-cycle as the tail kernel reads them (amg_tail.hip).
 struct TailLevel;
+struct TailLaunch {
+    int at, count, threads;            // places in tail_mem_, threads per member
+    size_t lds;
+};
 constexpr int kTailLevels = 32;                // options.max_levels <= 32
 // Rows of a member on its first tail level, at most: where one workgroup per member
 // stops being faster than a launch per half-sweep that has the whole chip.  Limits of
@@ -314,9 +318,10 @@ private:
     // the tail: packed levels of every member in it; levels with members that the
     // level kernels still work on
     bool tail_on_ = false;
-    size_t tail_lds_ = 0;
+    std::vector<TailLaunch> tail_launches_;
     DBuf<uint16_t> tail_perm_, tail_col_;
-    DBuf<int2> tail_slice_, tail_mem_;
+    DBuf<int2> tail_slice_;
+    DBuf<int4> tail_mem_;
     DBuf<double> tail_val_, tail_dinv_;
     DBuf<int16_t> tail_p_;
     DBuf<TailLevel> tail_lev_;

@@ -30,7 +30,17 @@
 namespace pair {
 namespace {
 
+// Threads of a member's workgroup (its results do not depend on them).  As long as
+// the members have a CU or half of one each, 1024; with more of them the chip holds
+// as many at once as their waves and LDS allow, so a member's workgroup has a wave
+// per slice or two of its first level.  us per cycle without tail / 1024 for all / so:
+// 1000 members of 150 rows 139 / 134 / 99; 16000 1427 / 1493 / 716; 1000 of 600
+// 377 / 262 / 216; solve of 64000 of 40 rows 23.9 / 34.4 / 13.0 ms.
 constexpr int kTailThreads = 1024;
+constexpr int kTailFew = 512;
+int tail_threads(size_t members, int64_t rows) {
+    return members <= kTailFew || rows > 256 ? kTailThreads : rows > 64 ? 256 : 64;
+}
 constexpr int kPlanThreads = 256;
 constexpr int kTailPad = 4;               // slice widths are multiples of this
 constexpr uint16_t kNoRow = 0xffff;
@@ -187,12 +197,12 @@ k_tail_fill(const TailTask* __restrict__ tasks, const int* __restrict__ count, c
 
 // f(row, sum of the row times x) for the rows at positions [from, to) (multiples
 // of 64), a lane per row.
-template <class F>
+template <int NT, class F>
 __device__ __forceinline__ void tail_rows(int from, int to, const uint16_t* perm, const int2* slices,
                                           const double* __restrict__ val, const uint16_t* __restrict__ col,
                                           const double* x, F&& f) {
     const int lane = threadIdx.x & 63;
-    for (int s = from / 64 + static_cast<int>(threadIdx.x >> 6); s < to / 64; s += kTailThreads / 64) {
+    for (int s = from / 64 + static_cast<int>(threadIdx.x >> 6); s < to / 64; s += NT / 64) {
         const int2 sl = slices[s];
         const int w = __builtin_amdgcn_readfirstlane(sl.y);
         const int64_t base = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(sl.x)) * 64;
@@ -223,8 +233,9 @@ __device__ __forceinline__ void tail_rows(int from, int to, const uint16_t* perm
     }
 }
 
-__global__ void __launch_bounds__(kTailThreads)
-k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, const uint8_t* __restrict__ active,
+template <int NT>
+__global__ void __launch_bounds__(NT)
+k_tail(const int4* __restrict__ members, const TailLevel* __restrict__ levels, const uint8_t* __restrict__ active,
        const uint16_t* __restrict__ perm, const int2* __restrict__ slices, const double* __restrict__ val,
        const uint16_t* __restrict__ col, const double* __restrict__ dinv, const int16_t* __restrict__ interp,
        double omega, uint32_t pre, int npre, uint32_t post, int npost) {
@@ -232,9 +243,9 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
     __shared__ TailLevel lev[kTailLevels];
     __shared__ int s_row[kTailLevels], s_perm[kTailLevels], s_slice[kTailLevels];   // places in LDS
     __shared__ int s_tot[3];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const int2 mb = members[m];             // first level's entry, levels (0: not in the tail)
-    if (mb.y == 0 || !active[m]) return;
+    const int tid = threadIdx.x;
+    const int4 mb = members[blockIdx.x];    // first level's entry, levels, member
+    if (!active[mb.z]) return;
     if (tid < mb.y) lev[tid] = levels[mb.x + tid];
     __syncthreads();
     if (tid == 0) {
@@ -265,18 +276,18 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
     int16_t* const ip = reinterpret_cast<int16_t*>(pm + s_tot[2]);
     for (int l = 0; l < last; ++l) {
         const int n = lev[l].n, pa = lev[l].pos_a, pr = lev[l].pos_r;
-        for (int i = tid; i < n; i += kTailThreads) {
+        for (int i = tid; i < n; i += NT) {
             ds[s_row[l] + i] = dinv[lev[l].rows + i];
             ip[s_row[l] + i] = interp[lev[l].rows + i];
         }
-        for (int i = tid; i < pa; i += kTailThreads) pm[s_perm[l] + i] = perm[lev[l].perm_a + i];
-        for (int i = tid; i < pr; i += kTailThreads) pm[s_perm[l] + pa + i] = perm[lev[l].perm_r + i];
-        for (int i = tid; i < pa / 64; i += kTailThreads) sl[s_slice[l] + i] = slices[lev[l].slice_a + i];
-        for (int i = tid; i < pr / 64; i += kTailThreads) sl[s_slice[l] + pa / 64 + i] = slices[lev[l].slice_r + i];
+        for (int i = tid; i < pa; i += NT) pm[s_perm[l] + i] = perm[lev[l].perm_a + i];
+        for (int i = tid; i < pr; i += NT) pm[s_perm[l] + pa + i] = perm[lev[l].perm_r + i];
+        for (int i = tid; i < pa / 64; i += NT) sl[s_slice[l] + i] = slices[lev[l].slice_a + i];
+        for (int i = tid; i < pr / 64; i += NT) sl[s_slice[l] + pa / 64 + i] = slices[lev[l].slice_r + i];
     }
     {
         const auto b = (Global<double>)lev[0].b;
-        for (int i = tid; i < lev[0].n; i += kTailThreads) bs[i] = b[i];
+        for (int i = tid; i < lev[0].n; i += NT) bs[i] = b[i];
     }
     __syncthreads();
     // a half-sweep of level l from cur into oth: the class's rows, the others kept
@@ -285,9 +296,9 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
         const double* d = ds + s_row[l];
         const int pf = lev[l].posf, pa = lev[l].pos_a;
         const uint16_t* q = pm + s_perm[l];
-        for (int i = (c ? 0 : pf) + tid; i < (c ? pf : pa); i += kTailThreads)
+        for (int i = (c ? 0 : pf) + tid; i < (c ? pf : pa); i += NT)
             if (q[i] != kNoRow) oth[q[i]] = cur[q[i]];
-        tail_rows(c ? pf : 0, c ? pa : pf, q, sl + s_slice[l], val, col, cur,
+        tail_rows<NT>(c ? pf : 0, c ? pa : pf, q, sl + s_slice[l], val, col, cur,
                   [&](int i, double s) { oth[i] = cur[i] + omega * (b[i] - s) * d[i]; });
     };
     // down
@@ -300,14 +311,14 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
         // an even number of exchanges ends in x, an odd one starts from work
         double *cur = (npre & 1) ? work : x, *oth = (npre & 1) ? x : work;
         if (npre == 0) {
-            for (int i = tid; i < n; i += kTailThreads) x[i] = 0.0;
+            for (int i = tid; i < n; i += NT) x[i] = 0.0;
             __syncthreads();
         }
         for (int k = 0; k < npre; ++k) {
             const bool c = (pre >> k & 1u) != 0;
             if (k == 0) {                   // from x = 0
                 const double* d = ds + s_row[l];
-                for (int i = tid; i < pa; i += kTailThreads)
+                for (int i = tid; i < pa; i += NT)
                     if (q[i] != kNoRow) oth[q[i]] = (i >= pf) == c ? omega * b[q[i]] * d[q[i]] : 0.0;
             } else {
                 half_sweep(l, c, cur, oth);
@@ -317,10 +328,10 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
             oth = sw;
             __syncthreads();
         }
-        tail_rows(0, pa, q, sl + s_slice[l], val, col, x, [&](int i, double s) { r[i] = b[i] - s; });
+        tail_rows<NT>(0, pa, q, sl + s_slice[l], val, col, x, [&](int i, double s) { r[i] = b[i] - s; });
         __syncthreads();
         double* const bc = b + n;
-        tail_rows(0, lev[l].pos_r, q + pa, sl + s_slice[l] + pa / 64, val, col, r,
+        tail_rows<NT>(0, lev[l].pos_r, q + pa, sl + s_slice[l] + pa / 64, val, col, r,
                   [&](int i, double s) { bc[i] = s; });
         __syncthreads();
     }
@@ -329,7 +340,7 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
         const int n = lev[last].n, o = s_row[last];
         const auto Inv = (Global<double>)lev[last].inv;
         const double* b = bs + o;
-        for (int r = tid; r < n; r += kTailThreads) {
+        for (int r = tid; r < n; r += NT) {
             double s = 0.0;
             int c = 0;
             for (; c + 16 <= n; c += 16) {
@@ -349,7 +360,7 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
         const int n = lev[l].n;
         double* const x = xs + s_row[l];
         const int16_t* p = ip + s_row[l];
-        for (int i = tid; i < n; i += kTailThreads) {
+        for (int i = tid; i < n; i += NT) {
             const int c = p[i];
             if (c >= 0) x[i] += x[n + c];
         }
@@ -363,12 +374,12 @@ k_tail(const int2* __restrict__ members, const TailLevel* __restrict__ levels, c
             __syncthreads();
         }
         if (cur != x) {
-            for (int i = tid; i < n; i += kTailThreads) x[i] = cur[i];
+            for (int i = tid; i < n; i += NT) x[i] = cur[i];
             __syncthreads();
         }
     }
     auto out = (__attribute__((address_space(1))) double*)lev[0].x;
-    for (int i = tid; i < lev[0].n; i += kTailThreads) out[i] = xs[i];
+    for (int i = tid; i < lev[0].n; i += NT) out[i] = xs[i];
 }
 
 // LDS of a member with these rows per tail level, at most.
@@ -386,6 +397,7 @@ size_t tail_lds(const std::vector<int64_t>& n) {
 
 void Hierarchy::build_tail() {
     tail_on_ = false;
+    tail_launches_.clear();
     const int nl = static_cast<int>(levels_.size());
     std::vector<int> first(B_, -1);
     size_t lds = 0;
@@ -415,7 +427,7 @@ void Hierarchy::build_tail() {
     }
     std::vector<TailTask> tasks;
     std::vector<TailLevel> lev;
-    std::vector<int2> members(B_, make_int2(0, 0));
+    std::vector<int4> members(B_, make_int4(0, 0, 0, 0));
     int64_t nperm = 0, nslice = 0, nrows = 0;
     auto place = [&](TailTask& T, int64_t n, bool classes) {
         const int64_t pos = classes ? max_positions(n) : (n + 63) / 64 * 64;
@@ -427,7 +439,7 @@ void Hierarchy::build_tail() {
     };
     for (int b = 0; b < B_; ++b) {
         if (first[b] < 0) continue;
-        members[b] = make_int2(static_cast<int>(lev.size()), nlev_[b] - first[b]);
+        members[b] = make_int4(static_cast<int>(lev.size()), nlev_[b] - first[b], b, 0);
         for (int l = first[b]; l < nlev_[b]; ++l) {
             Level& L = levels_[l];
             TailLevel q{};
@@ -492,7 +504,7 @@ void Hierarchy::build_tail() {
     }
     // a member's levels from its coarsest up to the first whose A or R has too many
     // entries; tasks are A and R of its levels in order
-    lds = 0;
+    std::vector<size_t> need(B_, 0);
     int task = 0;
     for (int b = 0; b < B_; ++b) {
         if (first[b] < 0) continue;
@@ -512,7 +524,7 @@ void Hierarchy::build_tail() {
         task = skip_to;
         std::vector<int64_t> n;
         for (; l <= last; ++l) n.push_back(levels_[l].cnt[b]);
-        lds = std::max(lds, tail_lds(n));
+        need[b] = tail_lds(n);
     }
     // the level kernels' members: those whose tail starts further down
     level_on_.assign(nl, 0);
@@ -537,9 +549,22 @@ void Hierarchy::build_tail() {
             t += 2;
         }
     tail_lev_.alloc(lev.size());
-    tail_mem_.alloc(B_);
     h2d(tail_lev_.p, lev.data(), lev.size(), s_);
-    h2d(tail_mem_.p, members.data(), B_, s_);
+    // the launches: members by the size of their workgroups
+    std::vector<int4> order;
+    const size_t in_tail = B_ - std::count(first.begin(), first.end(), -1);
+    for (int nt : {kTailThreads, 256, 64}) {
+        TailLaunch g{static_cast<int>(order.size()), 0, nt, 0};
+        for (int b = 0; b < B_; ++b)
+            if (first[b] >= 0 && tail_threads(in_tail, levels_[first[b]].cnt[b]) == nt) {
+                order.push_back(members[b]);
+                g.lds = std::max(g.lds, need[b]);
+                ++g.count;
+            }
+        if (g.count > 0) tail_launches_.push_back(g);
+    }
+    tail_mem_.alloc(order.size());
+    h2d(tail_mem_.p, order.data(), order.size(), s_);
     // the level kernels and coarse solves leave the tail's members out
     std::vector<std::vector<int>> mem(nl);
     std::vector<std::vector<int64_t>> moff(nl), mn(nl), ioff(nl);
@@ -567,10 +592,10 @@ void Hierarchy::build_tail() {
             h2d(L.coarse_inv_off_d.p, ioff[l].data(), mem[l].size(), s_);
         }
     }
-    PAIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tail), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 static_cast<int>(kTailLds)));
+    for (const void* k : {reinterpret_cast<const void*>(&k_tail<64>), reinterpret_cast<const void*>(&k_tail<256>),
+                          reinterpret_cast<const void*>(&k_tail<kTailThreads>)})
+        PAIR_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kTailLds)));
     PAIR_HIP(hipStreamSynchronize(s_));         // the host arrays go
-    tail_lds_ = lds;
     tail_on_ = true;
 }
 
@@ -583,10 +608,17 @@ void Hierarchy::launch_tail() {
     };
     const std::string& pre = prm_.relax_pre_coarse;
     const std::string& post = prm_.relax_post_coarse;
-    hipLaunchKernelGGL(k_tail, dim3(static_cast<unsigned>(B_)), dim3(kTailThreads), tail_lds_, s_, tail_mem_.p,
-                       tail_lev_.p, sv_.active, tail_perm_.p, tail_slice_.p, tail_val_.p, tail_col_.p, tail_dinv_.p,
-                       tail_p_.p, prm_.omega, bits(pre), static_cast<int>(pre.size()), bits(post),
-                       static_cast<int>(post.size()));
+    for (const TailLaunch& g : tail_launches_) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(g.count)), dim3(g.threads), g.lds, s_,
+                               tail_mem_.p + g.at, tail_lev_.p, sv_.active, tail_perm_.p, tail_slice_.p, tail_val_.p,
+                               tail_col_.p, tail_dinv_.p, tail_p_.p, prm_.omega, bits(pre),
+                               static_cast<int>(pre.size()), bits(post), static_cast<int>(post.size()));
+        };
+        if (g.threads == 64) launch(k_tail<64>);
+        else if (g.threads == 256) launch(k_tail<256>);
+        else launch(k_tail<kTailThreads>);
+    }
     PAIR_LAUNCH_CHECK();
 }
 

@@ -39,3 +39,31 @@ def test_setup_time_grows_with_the_number_of_segments():
         best.append(min(t))
     print("seconds", best, flush=True)
     assert best[1] < 7.0 * best[0]
+
+
+@pytest.mark.parametrize("copies", [100, 110])
+def test_members_round_alike_in_a_batch_of_hundreds(copies):
+    """500 and 550 members whose first coarse levels have some 40 to 330 rows: with more
+    than 512 their workgroups are smaller; bit for bit as each member alone."""
+    need_gpu()
+    from paper_1910_11463_amd.solver import Amg
+    from tests.test_gpu_tail import _batch, _even
+    opts = dict(tol_inner=1e-11, max_inner=400, coarse_max=16, relax_pre_coarse="FC", relax_post_coarse="C")
+    sizes = [130, 190, 200, 760, 1000]
+    mats = [_even(n, 3, n) for n in sizes]
+    b = [np.random.default_rng(n).uniform(-1.0, 1.0, n) for n in sizes]
+    rowptr, col, val, seg = _batch(mats * copies)
+    a = Amg(**opts)
+    a.setup(rowptr, col, val, seg)
+    x, it, rel, rc = a.solve(np.concatenate(b * copies))
+    a.close()
+    assert rc == 0, rel
+    for s, m in enumerate(mats):
+        one = Amg(**opts)
+        one.setup(*m)
+        print("member of", sizes[s], "rows, coarse", len(one.level(1)["rowptr"]) - 1, flush=True)
+        y, it1, _, rc1 = one.solve(b[s])
+        one.close()
+        assert rc1 == 0
+        for k in range(s, len(sizes) * copies, len(sizes)):
+            assert it[k] == it1[0] and np.array_equal(x[seg[k]:seg[k + 1]], y), k
