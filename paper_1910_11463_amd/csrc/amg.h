@@ -192,13 +192,16 @@ constexpr int64_t kTailRows = 2048;
 // Entries (padded) of A and of R of a member on a tail level, at most: one workgroup
 // gathers all of them in LDS in every pass (11000 cycles for 27000), which a launch
 // over the whole chip does not feel.  By the member alone, not by how many share the
-// launch, so that it rounds the same in any batch.  Single matrices, us per cycle
-// without tail / limits of 32768, 40960, 49152 / no limit, levels below the finest:
-// 666 and 176 rows of 20600 and 26000 entries 91.9 / 91.9, 88.9, 88.4 / 88.9;
-// 550 and 173 of 36400 and 29700 97.2 / 96.9, 97.0, 98.8 / 99.6; 610 and 212 of 49800
-// and 44800 103.5 / - / 111.6; 417 and 146 of 97100 and 21300 107.8 / - / 125.6.
-// 24 such of 791 and 219 rows of 24600 and 37700: 133.1 / 133.9, 134.0, 128.9 / 130.3.
-constexpr int kTailEntries = 49152;
+// launch, so that it rounds the same in any batch; what it costs a single matrix and
+// gives a batch is balanced at this limit.  us per cycle without tail / limits of 49152
+// and 65536 / no limit, first two coarse levels, single matrices: 671 and 174 rows of
+// 5700 and 5600 entries 87.0 / 70.4, 70.8 / 72.5; 252 on the second of 48600 111.9 /
+// 105.8, 108.0 / 110.3; 610 and 212 of 49800 and 44800 103.5 / 103.5, 111.6 / 111.6;
+// 325 of 74600 116.2 / 111.4, 111.2 / 127.9; 417 of 97100 107.8 / 107.8, 107.8 / 125.6.
+// Warm V(1,1) sweeps, ms: 12^3 tets S4 8.52 / 8.12, 7.94 / 7.91; 16^3 tets S2 11.8 /
+// 11.6, 11.0 / 11.0; 32^3 hexes S2 14.97 / 14.84, 14.85 / 15.37; 24^3 S4 12.11 / 11.89,
+// 11.90 / 12.93.
+constexpr int kTailEntries = 65536;
 constexpr size_t kTailLds = 150 * 1024;        // of the CU's 160 KB
 
 // A member's state after a convergence test, in pinned host memory.

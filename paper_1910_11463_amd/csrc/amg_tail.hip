@@ -485,8 +485,7 @@ void Hierarchy::build_tail() {
         }
     }
     const int nt = static_cast<int>(tasks.size());
-    // place numbers are 32-bit
-    if (nperm >= (int64_t(1) << 31) || nt >= (int64_t(1) << 31) / (kTailEntries / 64)) return;
+    if (nperm >= (int64_t(1) << 31)) return;       // place numbers are 32-bit
     std::vector<int> cnt(3 * static_cast<size_t>(nt), 0), entry(nt, -1);
     tail_perm_.alloc(std::max<int64_t>(nperm, 1));
     tail_slice_.alloc(std::max<int64_t>(nslice, 1));
@@ -520,6 +519,7 @@ void Hierarchy::build_tail() {
         for (; k < skip_to; ++k) {
             entry[k] = static_cast<int>(slots);
             slots += cnt[3 * k + 2];
+            if (slots >= (int64_t(1) << 31)) return;
         }
         task = skip_to;
         std::vector<int64_t> n;
