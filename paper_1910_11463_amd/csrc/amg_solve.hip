@@ -1392,6 +1392,24 @@ double residual_bytes(const Level& L, double vb = 8.0) {
            2.0 * n;
 }
 
+// The first half-sweep of a coarse level, done by the restriction that has just
+// formed b: 1/a_ii of the class's rows, cf and the whole output vector.
+double first_sweep_bytes(const Level& L, int which, double vb = 8.0) {
+    const double n = static_cast<double>(L.n_f + L.n_c);
+    return vb * static_cast<double>(which < 0 ? L.n_f : L.n_c) + 9.0 * n;
+}
+
+// A level that only the tail works on, per cycle: the packed entries (8-byte values,
+// 16-bit columns) of A in every half-sweep but the first and in the residual, those of
+// R, and once the row orders, 1/a_ii and the interpolation; b and x on its first level.
+double tail_bytes(const Level& L, const std::string& pre, const std::string& post, bool first) {
+    const double n = static_cast<double>(L.n_f + L.n_c);
+    double nnz = static_cast<double>(L.nnz_f + L.nnz_c) + static_cast<double>(L.R.nnz);
+    const std::string later = (pre.empty() ? pre : pre.substr(1)) + post;
+    for (char ch : later) nnz += static_cast<double>(ch == 'F' ? L.nnz_f : L.nnz_c);
+    return 10.0 * nnz + 12.0 * n + 2.0 * static_cast<double>(L.R.n) + (first ? 16.0 * n : 0.0);
+}
+
 double restrict_bytes(const Level& L, double vb = 8.0) {
     const double n = static_cast<double>(L.n_f + L.n_c);
     const double nc = static_cast<double>(L.R.n);
@@ -2012,7 +2030,8 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero, bool b_may_be_zero) {
 // Algorithmic bytes of one V-cycle over all members (FP64 vectors; matrix
 // values 8 B, or 4 B on FP32 coarse levels; int32 indices 4 B, int64 row
 // offsets 8 B): the relaxation schedules' half-sweeps, residual, restriction
-// and interpolation per level, the coarsest solves and the convergence test.
+// and interpolation per level, the coarsest solves and the convergence test.  Levels
+// on which some members are in the tail and others are not count as the others'.
 double Hierarchy::solve_bytes_per_cycle() const {
     double bytes = 0.0;
     const int nl = static_cast<int>(levels_.size());
@@ -2027,19 +2046,29 @@ double Hierarchy::solve_bytes_per_cycle() const {
         const std::string& pre = l == 0 ? prm_.relax_pre : prm_.relax_pre_coarse;
         const std::string& post = l == 0 ? prm_.relax_post : prm_.relax_post_coarse;
         const double vb = L.valf.p ? 4.0 : 8.0;
-        bool zero = l > 0;   // coarse levels start from x = 0
+        if (!level_on_[l]) {
+            bytes += tail_bytes(L, pre, post, level_on_[l - 1] != 0);
+            continue;
+        }
+        bool first = l > 0;   // coarse levels start from x = 0, in the restriction
+        if (first && pre.empty()) {
+            bytes += 8.0 * n;
+            first = false;
+        }
         for (const std::string* sc : {&pre, &post}) {
             for (char ch : *sc) {
                 const int which = ch == 'F' ? -1 : 1;
-                if (ch == 'T' && l == 0 && ell_ && ell_->tet_tiles) {
-                    bytes += tet_tile_relax_bytes(L, *ell_, zero);
+                if (first)
+                    bytes += first_sweep_bytes(L, which, vb);
+                else if (ch == 'T' && l == 0 && ell_ && ell_->tet_tiles) {
+                    bytes += tet_tile_relax_bytes(L, *ell_, false);
                 } else if (ch == 'T' && l == 0 && ell_) {
                     const int tz = prm_.tile_z > 0 ? std::min(prm_.tile_z, ell_->nz) : ell_->nz;
-                    bytes += tile_relax_bytes(L, *ell_, prm_.tile_xy, tz, zero);
+                    bytes += tile_relax_bytes(L, *ell_, prm_.tile_xy, tz, false);
                 } else
-                    bytes += (l == 0 && ell_) ? ell_relax_bytes(L, *ell_, which, zero)
-                                              : relax_bytes(L, which, zero, vb);
-                zero = false;
+                    bytes += (l == 0 && ell_) ? ell_relax_bytes(L, *ell_, which, false)
+                                              : relax_bytes(L, which, false, vb);
+                first = false;
             }
         }
         bytes += (l == 0 && ell_) ? ell_residual_bytes(L, *ell_) : residual_bytes(L, vb);
