@@ -171,8 +171,12 @@ typedef struct pair_stats {
     double op_complexity;     /* sum_l nnz_l / nnz_0, mean over directions      */
     int64_t level_n[PAIR_MAX_LEVELS];   /* direction 0: rows per level           */
     int64_t level_nnz[PAIR_MAX_LEVELS]; /* direction 0: nonzeros per level       */
-    double t_assemble_ms, t_setup_ms, t_solve_ms, t_other_ms; /* GPU-synchronised wall times,
-                                 summed over the streams (see pair_options.streams) */
+    double t_assemble_ms, t_setup_ms, t_solve_ms, t_other_ms; /* wall times summed over the
+                                 streams (see pair_options.streams), each ending with a wait
+                                 for the GPU except between the right-hand side and the
+                                 V-cycles: t_solve_ms holds the kernels of both, t_other_ms
+                                 the right-hand side's launches, the scalar-flux sums and
+                                 the copies of psi                                        */
     double bytes_solve;       /* algorithmic bytes moved by the V-cycle kernels  */
 } pair_stats;
 
@@ -326,7 +330,9 @@ int pair_export_fine_operator(pair_ctx* ctx, int m, int64_t* nnz, int64_t* rowpt
  * timed regions), pair_profile_enable(0) stops.  Launches inside a
  * hipGraph capture are not timed.  kind: 0 = FC-Jacobi half-sweeps on the
  * finest level (and tile sweeps), 1 = finest-level residual, 2 = restriction
- * from the finest level, 3 = half-sweeps on coarser levels, 4 = convergence-
+ * from the finest level, 3 = half-sweeps on coarser levels that are launches of
+ * their own (not the first one from x = 0, which the restriction does, nor those
+ * of levels that one workgroup per member runs in one launch), 4 = convergence-
  * test residual norm, 5 = setup: restriction rows with dense local systems
  * (lAIR on the levels below the finest), 6 = the same launches with each
  * gathered row of A counted once per launch (kind 5 counts it once per local

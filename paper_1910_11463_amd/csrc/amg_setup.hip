@@ -1988,8 +1988,9 @@ k_r_filter_copy(int64_t nc, const int32_t* __restrict__ c2f, const int64_t* __re
 // ------------------------------------------------------------- A P and R (A P)
 // One-point interpolation maps column j to coarse column p[j], so row i of A P
 // merges the entries of row i of A that share p[j]: keys (p[j], position) are
-// sorted and each run summed in position order (reproducible).  A P is stored
-// in the row slots of A (same row offsets) with ap_len[i] entries per row.
+// sorted and each run summed in position order (reproducible).  Row i of A P has
+// ap_len[i] entries from ap_start[i] on: its row's place in A, or packed where every
+// needed row has at most 16 entries (k_ap_reg).
 constexpr int RMAX = KCAP + 1;   // longest R row (kmax + 1)
 constexpr uint32_t HASH_EMPTY = 0xffffffffu;
 
@@ -2286,7 +2287,7 @@ template <int NT, bool NUMERIC>
 __device__ int rap_hash_row(int64_t I, int tbl, uint32_t* tkeys, int32_t* tpos, uint32_t* ucol,
                             double* uval, const int64_t* __restrict__ r_rowptr,
                             const int32_t* __restrict__ r_col, const double* __restrict__ r_val,
-                            const int64_t* __restrict__ rowptr, const int* __restrict__ ap_len,
+                            const int64_t* __restrict__ ap_start, const int* __restrict__ ap_len,
                             const int32_t* __restrict__ ap_col, const double* __restrict__ ap_val,
                             int32_t* __restrict__ out_col, double* __restrict__ out_val,
                             int* s_pref, int64_t* s_base, double* s_rv, int* s_cnt) {
@@ -2296,7 +2297,7 @@ __device__ int rap_hash_row(int64_t I, int tbl, uint32_t* tkeys, int32_t* tpos, 
     const uint32_t mask = static_cast<uint32_t>(tbl - 1);
     for (int t = tid; t < rl; t += NT) {
         const int64_t k = r_col[rs + t];
-        s_base[t] = rowptr[k];
+        s_base[t] = ap_start[k];
         s_pref[t + 1] = ap_len[k];
         s_rv[t] = r_val[rs + t];
     }
@@ -2367,7 +2368,7 @@ template <int NT, int TBL, bool NUMERIC>
 __global__ void __launch_bounds__(NT)
 k_rap_lds(int nrows, const int32_t* __restrict__ list, const int64_t* __restrict__ r_rowptr,
           const int32_t* __restrict__ r_col, const double* __restrict__ r_val,
-          const int64_t* __restrict__ rowptr, const int* __restrict__ ap_len,
+          const int64_t* __restrict__ ap_start, const int* __restrict__ ap_len,
           const int32_t* __restrict__ ap_col, const double* __restrict__ ap_val,
           int64_t* __restrict__ cnt_out, const int64_t* __restrict__ c_rowptr,
           int32_t* __restrict__ c_col, double* __restrict__ c_val) {
@@ -2382,7 +2383,7 @@ k_rap_lds(int nrows, const int32_t* __restrict__ list, const int64_t* __restrict
     for (int r = blockIdx.x; r < nrows; r += gridDim.x) {
         const int64_t I = list[r];
         int nl = rap_hash_row<NT, NUMERIC>(I, TBL, tkeys, tpos, ucol, uval, r_rowptr, r_col, r_val,
-                                           rowptr, ap_len, ap_col, ap_val,
+                                           ap_start, ap_len, ap_col, ap_val,
                                            NUMERIC ? c_col + c_rowptr[I] : nullptr,
                                            NUMERIC ? c_val + c_rowptr[I] : nullptr, s_pref, s_base,
                                            s_rv, s_cnt);
@@ -2404,7 +2405,7 @@ template <int NT, int PCAP, int TCAP>
 __global__ void __launch_bounds__(NT)
 k_rap_num(int nrows, const int32_t* __restrict__ list, const int64_t* __restrict__ r_rowptr,
           const int32_t* __restrict__ r_col, const double* __restrict__ r_val,
-          const int64_t* __restrict__ rowptr, const int* __restrict__ ap_len,
+          const int64_t* __restrict__ ap_start, const int* __restrict__ ap_len,
           const int32_t* __restrict__ ap_col, const double* __restrict__ ap_val,
           const int64_t* __restrict__ c_rowptr, int32_t* __restrict__ c_col, double* __restrict__ c_val) {
     constexpr int TBL = 2 * PCAP;
@@ -2429,7 +2430,7 @@ k_rap_num(int nrows, const int32_t* __restrict__ list, const int64_t* __restrict
         const int rl = static_cast<int>(r_rowptr[I + 1] - rs);
         for (int t = tid; t < rl; t += NT) {
             const int64_t k = r_col[rs + t];
-            s_base[t] = rowptr[k];
+            s_base[t] = ap_start[k];
             s_pref[t + 1] = ap_len[k];
             s_rv[t] = r_val[rs + t];
         }
@@ -2556,7 +2557,7 @@ template <bool NUMERIC>
 __global__ void __launch_bounds__(NUMERIC ? 64 : 256)
 k_rap_merge(int nrows, const int32_t* __restrict__ list, const int64_t* __restrict__ r_rowptr,
             const int32_t* __restrict__ r_col, const double* __restrict__ r_val,
-            const int64_t* __restrict__ rowptr, const int* __restrict__ ap_len,
+            const int64_t* __restrict__ ap_start, const int* __restrict__ ap_len,
             const int32_t* __restrict__ ap_col, const double* __restrict__ ap_val,
             int64_t* __restrict__ cnt_out, const int64_t* __restrict__ c_rowptr,
             int32_t* __restrict__ c_col, double* __restrict__ c_val,
@@ -2612,7 +2613,7 @@ k_rap_merge(int nrows, const int32_t* __restrict__ list, const int64_t* __restri
             rv[t] = 0.0;
             if (t < rl) {
                 const int64_t k = r_col[rs + t];
-                pos[t] = rowptr[k];
+                pos[t] = ap_start[k];
                 end[t] = pos[t] + ap_len[k];
                 rv[t] = r_val[rs + t];
             }
@@ -2678,7 +2679,7 @@ k_rap_global(int nrows, const int32_t* __restrict__ list, const int64_t* __restr
              uint32_t* __restrict__ kscr, int32_t* __restrict__ pscr, uint32_t* __restrict__ cscr,
              double* __restrict__ vscr, const int64_t* __restrict__ r_rowptr,
              const int32_t* __restrict__ r_col, const double* __restrict__ r_val,
-             const int64_t* __restrict__ rowptr, const int* __restrict__ ap_len,
+             const int64_t* __restrict__ ap_start, const int* __restrict__ ap_len,
              const int32_t* __restrict__ ap_col, const double* __restrict__ ap_val,
              int64_t* __restrict__ cnt_out, const int64_t* __restrict__ c_rowptr,
              int32_t* __restrict__ c_col, double* __restrict__ c_val, int* __restrict__ gpref,
@@ -2697,7 +2698,7 @@ k_rap_global(int nrows, const int32_t* __restrict__ list, const int64_t* __restr
     int64_t* base = glob ? gbase + static_cast<size_t>(r) * sld : s_base;
     double* rv = glob ? grv + static_cast<size_t>(r) * sld : s_rv;
     int nl = rap_hash_row<256, NUMERIC>(I, tbl, kscr + o, pscr + o, cscr + o / 2, vscr + o / 2,
-                                        r_rowptr, r_col, r_val, rowptr, ap_len, ap_col, ap_val,
+                                        r_rowptr, r_col, r_val, ap_start, ap_len, ap_col, ap_val,
                                         NUMERIC ? c_col + c_rowptr[I] : nullptr,
                                         NUMERIC ? c_val + c_rowptr[I] : nullptr, pref, base,
                                         rv, s_cnt);

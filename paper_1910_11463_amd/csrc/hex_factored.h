@@ -17,8 +17,8 @@ constexpr double kHexS2 = 1.4142135623730950488;      // sqrt 2
 
 // The eigenvalues sigma_t + kap_x lam_ex + kap_y lam_ey + kap_z lam_0 (lam =
 // 2 +- i sqrt2) of an element's diagonal block in the Kronecker-sum basis:
-// real part mr, imaginary parts mi, and 1 / |.|^2.  Depend only on sigma_t and
-// the direction, so a sweep can form them ahead of the element's face values.
+// real part mr, imaginary parts mi, and 1 / |.|^2.  (A tile sweep divides one of
+// the four per lane and forms its own.)
 struct HexDen {
     double mr, mi[2][2], inv[2][2];
 };

@@ -22,7 +22,8 @@ enum ProfKind : int {
     PROF_RELAX_FINE = 0,     // finest-level relaxation (F/C half-sweeps, tile sweeps)
     PROF_RESIDUAL_FINE = 1,  // r = b - A x on the finest level
     PROF_RESTRICT_FINE = 2,  // b_c = R r from the finest level
-    PROF_RELAX_COARSE = 3,   // half-sweeps on all coarser levels
+    PROF_RELAX_COARSE = 3,   // half-sweeps on coarser levels as launches of their own: not
+                             // the first one (in the restriction) nor the tail's levels
     PROF_NORM_FINE = 4,      // convergence test on the finest level
     PROF_RBUILD = 5,         // lAIR rows with dense local systems (coarser levels' setup)
     PROF_RBUILD_ONCE = 6,    // the same launches, a gathered row of A counted once per launch
