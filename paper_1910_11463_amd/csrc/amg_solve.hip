@@ -749,7 +749,7 @@ k_hex_tile(uint32_t E, int nx, int ny, int nz, int tz, int mx, int my, int mz,
     using SPlace = std::make_signed_t<Place>;
     constexpr int W = TXY + 1;                          // quads per row of the exchange buffer
     constexpr double kS2 = kHexS2;
-    constexpr double kC = 0.70710678118654752440;       // 1 / sqrt 2
+    constexpr double kC = kHexC;
     __shared__ double2 sh[2][4 * W * W];                // nodes a_z' = 0, 1; row and column 0: outside the box
     const uint32_t per = static_cast<uint32_t>(mx) * static_cast<uint32_t>(my) * static_cast<uint32_t>(mz);
     const uint32_t m = blockIdx.x / per;
@@ -892,11 +892,11 @@ k_hex_tile(uint32_t E, int nx, int ny, int nz, int tz, int mx, int my, int mz,
             const double zr = (gr * mr + gi * mi) * inv, zi = (gi * mr - gr * mi) * inv;
             // W along x, then y: this lane's node
             const double zro = quad_swap<0>(zr), zio = quad_swap<0>(zi);
-            const double pr = ex * (zr + zro) + fx * (zi - zio);
-            const double pi = ex * (zi + zio) - fx * (zr - zro);
+            const double pr = fma(fx, zi - zio, ex * (zr + zro));
+            const double pi = fma(-fx, zr - zro, ex * (zi + zio));
             const double pro = quad_swap<1>(pr), pio = quad_swap<1>(pi);
-            const double qr = ey * (pr + pro) + fy * (pi - pio);
-            const double qi = ey * (pi + pio) - fy * (pr - pro);
+            const double qr = fma(fy, pi - pio, ey * (pr + pro));
+            const double qi = fma(-fy, pr - pro, ey * (pi + pio));
             // along z: inflow side q_r, the other side -(q_r + sqrt2 q_i)
             const double2 bv = take(rb[q]);
             const double2 xn = make_double2(bv.x - qr, bv.y + (qr + kS2 * qi));
