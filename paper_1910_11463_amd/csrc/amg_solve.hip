@@ -1945,6 +1945,15 @@ bool Hierarchy::solve_in(void* scratch, bool x_is_zero) {
 
 bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero, bool b_may_be_zero) {
     Level& L0 = levels_[0];
+    // if a call below fails (no memory for a graph, say), kernels that write the pinned
+    // results are done before their owner can free them
+    struct Drain {
+        hipStream_t s;
+        bool done = false;
+        ~Drain() {
+            if (!done) (void)hipStreamSynchronize(s);
+        }
+    } drain{s_};
     // |b| per member and the initial state
     dispatch_lpr(L0.lpr, [&](auto lc) {
         constexpr int LPR = decltype(lc)::value;
@@ -2009,6 +2018,7 @@ bool Hierarchy::solve_impl(bool use_graph, bool x_is_zero, bool b_may_be_zero) {
         ++cycles;
         n_act = wait();
     }
+    drain.done = true;
     // per-member results (host vectors sized at setup: assign does not reallocate)
     std::fill(cf_h_.begin(), cf_h_.end(), 0.0);
     bool ok = true;
