@@ -18,7 +18,7 @@ struct Block {
 };
 void* pinned_malloc(size_t bytes) {
     void* p = nullptr;
-    if (hipHostMalloc(&p, bytes, hipHostMallocCoherent) == hipSuccess) return p;
+    if (hipHostMalloc(&p, bytes, hipHostMallocCoherent | hipHostMallocPortable) == hipSuccess) return p;
     (void)hipGetLastError();
     return nullptr;
 }
